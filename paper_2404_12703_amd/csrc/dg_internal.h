@@ -59,6 +59,7 @@ struct View {
   int cur;          // trace buffer read this stage (0: Utr0, 1: Utr1)
   int bpar;         // entry of bcnt this surface sweep counts in; it clears the other
   int viscous, riemann, source, shock;
+  int one;          // one sweep per stage (one_sweep): no volume sweep, no stored volume integral
   int split;        // split-form volume integral with Pirozzoli's two-point flux (Gauss-Lobatto)
   int visc_law;     // 0 constant viscosity, 1 Sutherland's law
   int alpha_smooth; // 1: raise alpha to half the largest face neighbour's indicator value
@@ -73,6 +74,13 @@ struct View {
 // caches: MI355X's 256 MB Infinity Cache keeps smaller working sets between
 // sweeps, and plain accesses serve those better
 constexpr size_t kStreamBytes = size_t(384) << 20;
+
+// Euler in the standard form takes one sweep per stage, also with shock
+// capturing while the blending factor is local to the element (the smoothing
+// option needs the neighbours' indicator values, hence a sweep of its own)
+inline bool one_sweep(const dg_params &p) {
+  return !p.viscous && !p.volume_flux && !(p.shock_capturing && p.alpha_smooth);
+}
 
 // offsets (in elements of `real`) inside the basis block, for n = N+1
 struct BasisOffsets {

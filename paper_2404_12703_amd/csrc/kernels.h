@@ -181,12 +181,12 @@ struct Smem {
 };
 
 template <int N, typename real>
-__device__ __forceinline__ void load_basis(Smem<N, real> &sb, const real *basis) {
+__device__ __forceinline__ void load_basis(Smem<N, real> &sb, const real *basis, int tid) {
   using S = Sz<N>;
   constexpr int n = S::n;
   BasisOffsets o(n);
-  for (int t = threadIdx.x; t < n * n; t += blockDim.x) sb.Dh[(t / n) * (n + 1) + t % n] = basis[o.Dhat + t];
-  for (int t = threadIdx.x; t < n; t += blockDim.x) {
+  for (int t = tid; t < n * n; t += blockDim.x) sb.Dh[(t / n) * (n + 1) + t % n] = basis[o.Dhat + t];
+  for (int t = tid; t < n; t += blockDim.x) {
     sb.lm[t] = basis[o.lm + t];
     sb.lp[t] = basis[o.lp + t];
     sb.lhm[t] = basis[o.lhm + t];
@@ -206,7 +206,7 @@ __global__ void __launch_bounds__(Sz<N>::threads) k_trace(const View<real> *view
   const View<real> v = select_view(views, blk_start, nreq, single, lblk);
   __shared__ Smem<N, real> sb;
   __shared__ real sU[epb][5 * Pad<n>::size];
-  load_basis<N, real>(sb, v.basis);
+  load_basis<N, real>(sb, v.basis, threadIdx.x);
   const int le = threadIdx.x / n3, a = threadIdx.x - le * n3;
   const int64_t e = (int64_t)lblk * epb + le;
   const bool active = le < epb && e < v.E;
@@ -370,12 +370,21 @@ __device__ __forceinline__ void prim2cons(const real *q, real gamma, real *U) {
 }
 
 // ---------------------------------------------------------------------------
-// Euler without shock capturing: one sweep per stage.  FillFlux (Riemann
-// flux of both sides' stored U traces), VolInt of F_adv through LDS one
-// direction at a time, the SurfInt gather, ApplyJac, the stage update and the
-// next U traces.  mode 0: du = A du + dt R, U += B du; mode 1: write R only.
+// Euler, with or without shock capturing: one sweep per stage.  Nothing of
+// the inviscid operator waits for a neighbour's result (the blending factor
+// is local to the element unless it is smoothed), so the state, the metrics
+// and the register cross HBM once: FillFlux (Riemann flux of this side's
+// recomputed U trace and the neighbour's stored one), VolInt of F_adv through
+// LDS one direction at a time, the SurfInt gather, ApplyJac, the stage update
+// and the next U traces.  mode 0: du = A du + dt R, U += B du; mode 1: write
+// R only.  SHOCK: the element's indicator value comes first; a workgroup with
+// a blended element is listed for k_blend and stops.
+// Bound by HBM: 8 (36 + 13 f) bytes per node, f = 6/(N+1) face nodes per node,
+// with every load issued before the phase that precedes its use.  A second
+// buffer of flux rows (two barriers fewer) measured the same at N = 5 and 3%
+// slower at N = 4.
 // ---------------------------------------------------------------------------
-template <int N, typename real>
+template <int N, typename real, bool SHOCK, bool LGL, bool NT>
 __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<real> *views, const int *blk_start,
                                                                       int nreq, View<real> single, int mode) {
   using S = Sz<N>;
@@ -383,78 +392,169 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   int lblk;
   const View<real> v = select_view(views, blk_start, nreq, single, lblk);
   __shared__ Smem<N, real> sb;
-  // contravariant fluxes of one direction (rows of n3), later the updated
-  // state (padded rows) for the next traces
-  __shared__ real sB[epb][5 * Pad<n>::size];
-  __shared__ real sS[epb][5][nf];
-  load_basis<N, real>(sb, v.basis);
+  // per element: the state in padded rows (this side's traces; then the flux
+  // rows of one direction; at the end the new state) and the face fluxes
+  // (before them the indicator's rows)
+  constexpr int rows = 5 * Pad<n>::size, faces = 5 * nf;
+  __shared__ real sA[epb][rows + faces];
+  __shared__ real sAl[epb];
+  load_basis<N, real>(sb, v.basis, threadIdx.x);
+  if (SHOCK && lblk == 0 && threadIdx.x == 0) v.bcnt[1 - v.bpar] = 0;  // the next sweep's count
   const int le = threadIdx.x / n3, a = threadIdx.x - le * n3;
   const int64_t e = (int64_t)lblk * epb + le;
   const bool active = le < epb && e < v.E;
-  real *const sm = sB[le < epb ? le : 0];
+  real *const su = sA[le < epb ? le : 0];
+  real *const sf = su + rows;
   const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
   const uint32_t vi = (uint32_t)(e * n3 + a), fb = (uint32_t)(e * 6 * n2);
   const real gam = v.gamma, rR = v.rRgas;
   const Bg<real> bg{v.bg_p, v.bg_H};
   const real *tr = v.cur ? v.Utr1 : v.Utr0;
   const int i = a % n, j = (a / n) % n, k = a / n2;
+  constexpr bool plane_waves = n2 == 64 && epb == 1;  // a wave is one face of one element
+  const int pa = Pad<n>::at(i, j, k);
+  constexpr int upt = (nf + n3 - 1) / n3;  // face nodes per thread
+  double Uold[5] = {0, 0, 0, 0, 0};
+  real Un[5], ns[3];
+  bool prim = false;
+  real Ja[9];
+  // the neighbour's trace and the normal at face node fn
+  auto fetch = [&](int fn) {
+    int f = fn / n2;
+    if constexpr (plane_waves) f = __builtin_amdgcn_readfirstlane(f);
+    const int pq = fn - f * n2;
+    const int2 c = v.conn[e * 6 + f];
+    prim = (c.y >> 3) & 1;
+    int pp, qq;
+    orient_map(c.y & 7, pq % n, pq / n, N, pp, qq);
+    const uint32_t in = (uint32_t)c.x * n2 + pp + n * qq;
+#pragma unroll
+    for (int s = 0; s < 5; ++s) Un[s] = (tr + s * Ef)[in];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) ns[d] = (v.NS + d * Ef)[fb + fn];
+  };
   if (active) {
-    // FillFlux for the six faces of this element (face nodes spread over the threads)
-    for (int fn = a; fn < nf; fn += n3) {
-      const int f = fn / n2, pq = fn - f * n2, p = pq % n, q = pq / n;
-      const int2 c = v.conn[e * 6 + f];
-      const bool primary = (c.y >> 3) & 1;
-      int pp, qq;
-      orient_map(c.y & 7, p, q, N, pp, qq);
-      const uint32_t io = fb + fn, in = (uint32_t)c.x * n2 + pp + n * qq;
-      const uint32_t im = primary ? io : in, is = primary ? in : io;
-      real Um[5], Us[5], Pm[6], Ps[6];
 #pragma unroll
-      for (int s = 0; s < 5; ++s) {
-        Um[s] = (tr + s * Ef)[im];
-        Us[s] = (tr + s * Ef)[is];
+    for (int c = 0; c < 5; ++c) Uold[c] = ld<NT>(v.U + c * Ev + vi);
+    // the first face node's operands beside the state; with more than one per
+    // thread (N <= 4) the others' where they are used: held from here they
+    // spilled at N = 4
+    if (a < nf) fetch(a);
+#pragma unroll
+    for (int c = 0; c < 9; ++c) Ja[c] = ld<NT>(v.Ja + c * Ev + vi);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) su[c * Pad<n>::size + pa] = to_real(Uold[c], c, v);
+  }
+  if constexpr (SHOCK) {
+    real eps = real(0);  // rho p
+    if (active) {
+      real U[5], P[6];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) U[c] = to_real(Uold[c], c, v);
+      cons2prim(U, gam, rR, P, bg);
+      eps = P[0] * full_p(P[4], bg);
+    }
+    // the indicator's rows in the face area: V^-1, three line transforms, and
+    // the energies (over the dead first two rows where they need whole rows)
+    constexpr bool waves = (n3 % 64 == 0) || epb == 1;
+    constexpr int en = waves ? (n3 + 63) / 64 : n3;
+    static_assert(n2 + 3 * n3 + (waves ? 4 : 2) * en <= faces, "the indicator's rows must fit the face area");
+    const BasisOffsets o(n);
+    real *const r = sf + n2;
+    real al;
+    if constexpr (waves)
+      al = indicator_raw<N, real>(v, v.basis + o.Vinv, r, r + n3, r + 2 * n3, r + 3 * n3, r + 3 * n3 + en,
+                                  r + 3 * n3 + 2 * en, r + 3 * n3 + 3 * en, sf, active, a, eps);
+    else
+      al = indicator_raw<N, real>(v, v.basis + o.Vinv, r, r + n3, r + 2 * n3, r, r + n3, r + 3 * n3, r + 4 * n3, sf,
+                                  active, a, eps);
+    if (le < epb && a == 0) {
+      if (active) {
+        v.alpha_raw[e] = al;
+        if (v.alpha_in) al = v.alpha_in[e];
+        v.alpha[e] = al;
       }
-      cons2prim(Um, gam, rR, Pm, bg);
-      cons2prim(Us, gam, rR, Ps, bg);
-      real nsv[3];
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        const real ns = (v.NS + d * Ef)[io];
-        nsv[d] = primary ? ns : -ns;
-      }
-      const real sh = sqrt(nsv[0] * nsv[0] + nsv[1] * nsv[1] + nsv[2] * nsv[2]);
-      const real ish = real(1) / sh;
-      const real nv[3] = {nsv[0] * ish, nsv[1] * ish, nsv[2] * ish};
-      real Fs[5];
-      if (v.riemann == 1) riemann_roe(Um, Pm, Us, Ps, nv, gam, Fs, bg);
-      else riemann_llf(Um, Pm, Us, Ps, nv, gam, Fs, bg);
-#pragma unroll
-      for (int s = 0; s < 5; ++s) sS[le][s][fn] = primary ? Fs[s] * sh : -(Fs[s] * sh);
+      sAl[le] = active ? al : real(0);
     }
   }
-  real Ja[9], Fx[5], Fy[5], Fz[5];
-  double Uold[5] = {0, 0, 0, 0, 0};
+  __syncthreads();
+  if constexpr (SHOCK) {
+    bool any = false;
+#pragma unroll
+    for (int q = 0; q < epb; ++q) any = any || sAl[q] > real(0);
+    if (any) {  // left to the blend pass
+      if (threadIdx.x == 0) v.blist[atomicAdd(v.bcnt + v.bpar, 1)] = lblk;
+      return;
+    }
+  }
   if (active) {
+    // FillFlux for the six faces of this element
+#pragma unroll
+    for (int r = 0; r < upt; ++r) {
+      const int fn = a + r * n3;
+      if (fn < nf) {
+        if (r > 0) fetch(fn);
+        int f = fn / n2;
+        if constexpr (plane_waves) f = __builtin_amdgcn_readfirstlane(f);
+        const int pq = fn - f * n2;
+        int base, stride;
+        Pad<n>::face_line(f, pq, base, stride);
+        real Uo[5];
+        face_state<n, LGL>(su, (f & 1) ? sb.lp : sb.lm, base, stride, f & 1, Uo);
+        const bool primary = prim;
+        real Um[5], Us[5], Pm[6], Ps[6];
+#pragma unroll
+        for (int s = 0; s < 5; ++s) {
+          Um[s] = primary ? Uo[s] : Un[s];
+          Us[s] = primary ? Un[s] : Uo[s];
+        }
+        cons2prim(Um, gam, rR, Pm, bg);
+        cons2prim(Us, gam, rR, Ps, bg);
+        real nsv[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) nsv[d] = primary ? ns[d] : -ns[d];
+        const real sh = sqrt(nsv[0] * nsv[0] + nsv[1] * nsv[1] + nsv[2] * nsv[2]);
+        const real ish = real(1) / sh;
+        const real nv[3] = {nsv[0] * ish, nsv[1] * ish, nsv[2] * ish};
+        real Fs[5];
+        if (v.riemann == 1) riemann_roe(Um, Pm, Us, Ps, nv, gam, Fs, bg);
+        else riemann_llf(Um, Pm, Us, Ps, nv, gam, Fs, bg);
+#pragma unroll
+        for (int s = 0; s < 5; ++s) sf[s * nf + fn] = primary ? Fs[s] * sh : -(Fs[s] * sh);
+      }
+    }
+  }
+  // 1/J and the RK register, loaded before the volume integral: their latency
+  // overlaps it, and the register's loads precede its stores
+  real iJ = real(0);
+  double dUo[5] = {0, 0, 0, 0, 0};
+  real Fx[5], Fy[5], Fz[5];
+  if (active) {
+    // the FP64 copy in LDS is exact: read back rather than held through the
+    // face phase (those registers spilled at N = 3 to 5)
+    if constexpr (sizeof(real) == sizeof(double)) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) Uold[c] = su[c * Pad<n>::size + pa];
+    }
     real U[5], P[6];
 #pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      Uold[c] = (v.U + c * Ev)[vi];
-      U[c] = to_real(Uold[c], c, v);
-    }
+    for (int c = 0; c < 5; ++c) U[c] = to_real(Uold[c], c, v);
     cons2prim(U, gam, rR, P, bg);
+    iJ = v.invJ[vi];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) dUo[c] = (mode == 0 && v.rkA != 0.0) ? ld<NT>(v.dU + c * Ev + vi) : 0.0;
     flux_adv<0>(U, P, Fx, bg);
     flux_adv<1>(U, P, Fy, bg);
     flux_adv<2>(U, P, Fz, bg);
-#pragma unroll
-    for (int c = 0; c < 9; ++c) Ja[c] = (v.Ja + c * Ev)[vi];
   }
-  // VolInt: one computational direction at a time through LDS
+  __syncthreads();  // the state rows are read above; flux rows cover them
+  // VolInt: one computational direction at a time
   real V[5] = {0, 0, 0, 0, 0};
 #pragma unroll
   for (int ci = 0; ci < 3; ++ci) {
     if (active) {
 #pragma unroll
-      for (int c = 0; c < 5; ++c) sm[c * n3 + a] = Ja[3 * ci + 0] * Fx[c] + Ja[3 * ci + 1] * Fy[c] + Ja[3 * ci + 2] * Fz[c];
+      for (int c = 0; c < 5; ++c) su[c * n3 + a] = Ja[3 * ci + 0] * Fx[c] + Ja[3 * ci + 1] * Fy[c] + Ja[3 * ci + 2] * Fz[c];
     }
     __syncthreads();
     if (active) {
@@ -464,20 +564,13 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
         const int src = ci == 0 ? vnode(n, alp, j, k) : (ci == 1 ? vnode(n, i, alp, k) : vnode(n, i, j, alp));
         const real dh = sb.Dh[idx * (n + 1) + alp];
 #pragma unroll
-        for (int c = 0; c < 5; ++c) V[c] += dh * sm[c * n3 + src];
+        for (int c = 0; c < 5; ++c) V[c] += dh * su[c * n3 + src];
       }
     }
     __syncthreads();
   }
   double Unew[5] = {0, 0, 0, 0, 0};
   if (active) {
-    // 1/J and the RK register, loaded before the gather: their latency
-    // overlaps it, and the register's five loads precede its five stores
-    // (which the compiler could not move them across)
-    const real iJ = v.invJ[vi];
-    double dUo[5];
-#pragma unroll
-    for (int c = 0; c < 5; ++c) dUo[c] = (mode == 0 && v.rkA != 0.0) ? (v.dU + c * Ev)[vi] : 0.0;
     // SurfInt gather (one writer per entry) and ApplyJac
     const int pqf[3] = {j + n * k, i + n * k, i + n * j};
     const int lf[3] = {i, j, k};
@@ -486,7 +579,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
       const int d = f >> 1;
       const real lh = (f & 1) ? sb.lhp[lf[d]] : sb.lhm[lf[d]];
 #pragma unroll
-      for (int c = 0; c < 5; ++c) V[c] += sS[le][c][f * n2 + pqf[d]] * lh;
+      for (int c = 0; c < 5; ++c) V[c] += sf[c * nf + f * n2 + pqf[d]] * lh;
     }
     double R[5];
 #pragma unroll
@@ -507,34 +600,35 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
     } else {
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
-        double *dUc = v.dU + c * Ev;
         // the first stage (A = 0) does not read the register: whatever it
         // holds (a restored state, an aborted step) cannot leak into the step
         const double du = (v.rkA != 0.0 ? v.rkA * dUo[c] : 0.0) + v.dt * R[c];
-        dUc[vi] = du;
+        st<NT>(du, v.dU + c * Ev + vi);
         Unew[c] = Uold[c] + v.rkB * du;
-        (v.U + c * Ev)[vi] = Unew[c];
+        st<NT>(Unew[c], v.U + c * Ev + vi);
       }
     }
   }
   if (mode == 0) {
-    // ProlongToFace of the updated state for the next stage (the last
-    // barrier of the volume integral precedes these writes)
+    // ProlongToFace of the updated state for the next stage (the last barrier
+    // of the volume integral precedes these writes)
     if (active) {
 #pragma unroll
-      for (int c = 0; c < 5; ++c) sm[c * Pad<n>::size + Pad<n>::at(i, j, k)] = to_real(Unew[c], c, v);
+      for (int c = 0; c < 5; ++c) su[c * Pad<n>::size + pa] = to_real(Unew[c], c, v);
     }
     __syncthreads();
     if (active) {
       real *trn = v.cur ? v.Utr0 : v.Utr1;
       for (int fn = a; fn < nf; fn += n3) {
-        const int f = fn / n2, pq = fn - f * n2;
+        int f = fn / n2;
+        if constexpr (plane_waves) f = __builtin_amdgcn_readfirstlane(f);
+        const int pq = fn - f * n2;
         int base, stride;
         Pad<n>::face_line(f, pq, base, stride);
         real t[5];
-        prolong_state<n>(sm, (f & 1) ? sb.lp : sb.lm, base, stride, t);
+        face_state<n, LGL>(su, (f & 1) ? sb.lp : sb.lm, base, stride, f & 1, t);
 #pragma unroll
-        for (int c = 0; c < 5; ++c) (trn + c * Ef)[fb + fn] = t[c];
+        for (int c = 0; c < 5; ++c) st<NT>(t[c], trn + c * Ef + fb + fn);
       }
     }
   }
@@ -547,19 +641,24 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
 // primitives are reconstructed with minmod slopes (zero in the two boundary
 // subcells) and joined by the LLF flux.  `rows` are 16 LDS rows of n3 values
 // of this element: 0-4 primitives, 5-7 the metric of one direction, 8-10
-// w_l (D Ja)_l, 11-15 interface fluxes.  sFV holds D, w, x, xhalf.  Every
+// w_l (D Ja)_l, 11-15 interface fluxes.  sFV holds SubOps.  Every
 // thread of the workgroup calls it: it holds barriers.  Adds the subcell
 // term at this node to Vfv (the sign convention of the DG volume integral).
 // ---------------------------------------------------------------------------
+// the 1-D operators of the subcells in LDS: D, w, 1/w, the distances from a
+// node down and up to its interfaces, 1/(distance to the next node)
+template <int n>
+struct SubOps {
+  static constexpr int D = 0, w = n * n, rw = w + n, lo = rw + n, hi = lo + n, rdx = hi + n, size = rdx + n;
+};
+
 template <int N, typename real>
 __device__ __forceinline__ void fv_subcells(real *rows, const real *sFV, bool active, int a, int i, int j, int k,
                                             const real *P, const real *Ja, real gam, real rR, Bg<real> bg,
                                             real *Vfv) {
   constexpr int n = N + 1, n3 = n * n * n;
-  const real *Dm = sFV;
-  const real *wq = sFV + n * n;
-  const real *xq = sFV + n * n + n;
-  const real *xh = sFV + n * n + 2 * n;
+  using Q = SubOps<n>;
+  const real *Dm = sFV + Q::D, *wq = sFV + Q::w, *rw = sFV + Q::rw, *rdx = sFV + Q::rdx;
   if (active) {
 #pragma unroll
     for (int c = 0; c < 5; ++c) rows[c * n3 + a] = P[c];
@@ -592,7 +691,9 @@ __device__ __forceinline__ void fv_subcells(real *rows, const real *sFV, bool ac
         Jh[c] = acc;
       }
       const real sh = sqrt(Jh[0] * Jh[0] + Jh[1] * Jh[1] + Jh[2] * Jh[2]);
-      const real nv[3] = {Jh[0] / sh, Jh[1] / sh, Jh[2] / sh};
+      const real ish = real(1) / sh;
+      const real nv[3] = {Jh[0] * ish, Jh[1] * ish, Jh[2] * ish};
+      const real rd = rdx[l], rdm = rdx[l >= 1 ? l - 1 : 0], rdp = rdx[l + 1], up = sFV[Q::hi + l], dn = sFV[Q::lo + l + 1];
       real qL[5], qR[5];
 #pragma unroll
       for (int c = 0; c < 5; ++c) {
@@ -601,14 +702,14 @@ __device__ __forceinline__ void fv_subcells(real *rows, const real *sFV, bool ac
         real s0 = real(0), s1 = real(0);
         if (l >= 1) {
           const real qm = rows[c * n3 + lnode<n>(d, l - 1, pp, qq)];
-          s0 = minmod2((q0 - qm) / (xq[l] - xq[l - 1]), (q1 - q0) / (xq[l + 1] - xq[l]));
+          s0 = minmod2((q0 - qm) * rdm, (q1 - q0) * rd);
         }
         if (l + 1 <= N - 1) {
           const real q2 = rows[c * n3 + lnode<n>(d, l + 2, pp, qq)];
-          s1 = minmod2((q1 - q0) / (xq[l + 1] - xq[l]), (q2 - q1) / (xq[l + 2] - xq[l + 1]));
+          s1 = minmod2((q1 - q0) * rd, (q2 - q1) * rdp);
         }
-        qL[c] = q0 + s0 * (xh[l + 1] - xq[l]);
-        qR[c] = q1 - s1 * (xq[l + 1] - xh[l + 1]);
+        qL[c] = q0 + s0 * up;
+        qR[c] = q1 - s1 * dn;
       }
       real UL[5], UR[5], PL[6], PR[6], F[5];
       prim2cons(qL, gam, UL);
@@ -626,7 +727,7 @@ __device__ __forceinline__ void fv_subcells(real *rows, const real *sFV, bool ac
         real r = real(0);
         if (l < N) r += rows[(11 + c) * n3 + a];
         if (l > 0) r -= rows[(11 + c) * n3 + lnode<n>(d, l - 1, pp, qq)];
-        Vfv[c] += r / wq[l];
+        Vfv[c] += r * rw[l];
       }
     }
     __syncthreads();
@@ -737,7 +838,7 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
   // (D + D-hat)/16, rows padded to n + 1: the weights of the two-point sums
   // (two_point_kep_sums), exact scaling by a power of two
   __shared__ real sDs[SPLIT ? n * (n + 1) : 1];
-  load_basis<N, real>(sb, v.basis);
+  load_basis<N, real>(sb, v.basis, threadIdx.x);
   if constexpr (SPLIT) {
     const BasisOffsets o(n);
     for (int t = threadIdx.x; t < n * n; t += blockDim.x)
@@ -1349,10 +1450,12 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
 // the next U traces.  SH = 1 (shock capturing, first pass) also forms the
 // blending factors and hands a workgroup with a blended element to the blend
 // pass; SH = 2 (the blend pass) adds the FV subcell operator, and with SPLIT
-// takes the split form's advective volume integral for the blend.
+// takes the split form's advective volume integral for the blend.  ONE (the
+// blend pass after the one-sweep Euler kernel): there is no stored volume
+// integral, the advective one formed here is the whole of it.
 // ---------------------------------------------------------------------------
-template <int N, typename real, int SH, bool LGL, bool SPLIT = false, bool NT = false>
-__device__ __forceinline__ void surface_body(const View<real> &v, const int lblk, const int mode) {
+template <int N, typename real, int SH, bool LGL, bool SPLIT = false, bool NT = false, bool ONE = false>
+__device__ __forceinline__ void surface_body(const View<real> &v, const int lblk, const int mode, const int tid) {
   using S = Sz<N>;
   constexpr int n = S::n, n2 = S::n2, n3 = S::n3, nf = S::nf, epb = S::epb;
   constexpr bool SHOCK = SH != 0, FV = SH == 2;
@@ -1362,22 +1465,27 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
   // the blend pass: 16 rows per element for the subcell operator and the
   // advective volume integral, the 1-D operators of the subcells
   __shared__ real sX[FV ? epb * 16 * n3 : 1];
-  __shared__ real sFV[FV ? (n * n + 3 * n + 1) : 1];  // D, w, x, xhalf
+  __shared__ real sFV[FV ? SubOps<n>::size : 1];
   __shared__ real sAl[epb];
-  load_basis<N, real>(sb, v.basis);
+  load_basis<N, real>(sb, v.basis, tid);
   // the first pass clears the count of the next sweep (which alternates
   // entries, so no pass reads a count that another pass clears)
-  if (SH == 1 && lblk == 0 && threadIdx.x == 0) v.bcnt[1 - v.bpar] = 0;
+  if (SH == 1 && lblk == 0 && tid == 0) v.bcnt[1 - v.bpar] = 0;
   if constexpr (FV) {
+    using Q = SubOps<n>;
     const BasisOffsets o(n);
-    for (int t = threadIdx.x; t < n * n; t += blockDim.x) sFV[t] = v.basis[o.D + t];
-    for (int t = threadIdx.x; t < n; t += blockDim.x) {
-      sFV[n * n + t] = v.basis[o.w + t];
-      sFV[n * n + n + t] = v.basis[o.x + t];
+    for (int t = tid; t < n * n; t += blockDim.x) sFV[Q::D + t] = v.basis[o.D + t];
+    for (int t = tid; t < n; t += blockDim.x) {
+      const real w = v.basis[o.w + t], x = v.basis[o.x + t];
+      sFV[Q::w + t] = w;
+      sFV[Q::rw + t] = real(1) / w;
+      // from the node to its two subcell interfaces, and 1/(distance to the next node)
+      sFV[Q::lo + t] = x - v.basis[o.xhalf + t];
+      sFV[Q::hi + t] = v.basis[o.xhalf + t + 1] - x;
+      sFV[Q::rdx + t] = t + 1 < n ? real(1) / (v.basis[o.x + t + 1] - x) : real(0);
     }
-    for (int t = threadIdx.x; t < n + 1; t += blockDim.x) sFV[n * n + 2 * n + t] = v.basis[o.xhalf + t];
   }
-  const int le = threadIdx.x / n3, a = threadIdx.x - le * n3;
+  const int le = tid / n3, a = tid - le * n3;
   const int64_t e = (int64_t)lblk * epb + le;
   const bool active = le < epb && e < v.E;
   const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
@@ -1438,7 +1546,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
     if constexpr (SH == 1) {
       // a workgroup with a blended element is left to the blend pass
       if (any) {
-        if (threadIdx.x == 0) v.blist[atomicAdd(v.bcnt + v.bpar, 1)] = lblk;
+        if (tid == 0) v.blist[atomicAdd(v.bcnt + v.bpar, 1)] = lblk;
         return;
       }
     }
@@ -1540,7 +1648,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
         }
         __syncthreads();
       }
-      if (active && al > real(0)) {
+      if (active && (ONE || al > real(0))) {
         real Va[5] = {0, 0, 0, 0, 0};
         const real Hn = SPLIT ? rows[14 * n3 + a] : real(0);
 #pragma unroll
@@ -1551,7 +1659,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
             const int src = ci == 0 ? vnode(n, alp, j, k) : (ci == 1 ? vnode(n, i, alp, k) : vnode(n, i, j, alp));
             const real dh = sb.Dh[idx * (n + 1) + alp];
             if constexpr (SPLIT) {
-              const real ds = sFV[idx * n + alp] + dh;  // D + D-hat
+              const real ds = sFV[SubOps<n>::D + idx * n + alp] + dh;  // D + D-hat
               real F[5];
               two_point_kep(P[0], P[1], P[2], P[3], P[4], Hn, rows[src], rows[n3 + src], rows[2 * n3 + src],
                             rows[3 * n3 + src], rows[4 * n3 + src], rows[14 * n3 + src],
@@ -1567,7 +1675,11 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
           }
         }
 #pragma unroll
-        for (int c = 0; c < 5; ++c) Vb[c] = al * (Vfv[c] - Va[c]);
+        for (int c = 0; c < 5; ++c) Vb[c] = al > real(0) ? al * (Vfv[c] - Va[c]) : real(0);
+        if constexpr (ONE) {
+#pragma unroll
+          for (int c = 0; c < 5; ++c) Vb[c] += Va[c];
+        }
       }
     }
   }
@@ -1575,7 +1687,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
   if (active) {
     real V[5];
 #pragma unroll
-    for (int c = 0; c < 5; ++c) V[c] = ld<NT>(v.Vol + c * Ev + vi) + Vb[c];
+    for (int c = 0; c < 5; ++c) V[c] = ONE ? Vb[c] : ld<NT>(v.Vol + c * Ev + vi) + Vb[c];
     // 1/J and the RK register, loaded with the volume integral: their latency
     // overlaps the gather, and the register's five loads precede its five
     // stores (which the compiler could not move them across)
@@ -1656,16 +1768,20 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_surface(const V
                                                                           int nreq, View<real> single, int mode) {
   int lblk;
   const View<real> v = select_view(views, blk_start, nreq, single, lblk);
-  surface_body<N, real, SH, LGL, false, NT>(v, lblk, mode);
+  surface_body<N, real, SH, LGL, false, NT>(v, lblk, mode, threadIdx.x);
 }
 
 // Blend pass: the surface sweep with the FV subcell blend, for the workgroups
-// that k_surface<SH = 1> listed, request by request; a fixed grid strides over
-// each list.  The compiler hoists the body's invariant work out of the loop
-// and takes up to 256 VGPRs (one workgroup per SIMD); an out-of-line body
-// needs half, but its call stack made every launch, empty ones included,
-// 8 us slower, and the pass rarely has more than a few workgroups.
-template <int N, typename real, bool LGL, bool SPLIT>
+// that the sweep before it listed, request by request; a fixed grid strides
+// over each list.  The view's 100 scalar registers live across the loop, so
+// the compiler takes about 250 VGPRs: two 256-thread workgroups per CU, one
+// of 512.  Its time is the latency of a workgroup (about 19 us at N = 5, 30 us
+// at N = 7) times the rounds.  The thread index is opaque to the loop: hoisted
+// address arithmetic took another 45 registers and with them the second
+// workgroup.  An out-of-line body needs 134 VGPRs, but its call stack made
+// every launch, empty ones included, 8 us slower; the view reloaded in each
+// round needs 197 and was 10% slower.
+template <int N, typename real, bool LGL, bool SPLIT, bool ONE = false>
 __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_blend(const View<real> *views, int nreq,
                                                                         View<real> single, int mode) {
   const int nr = nreq == 0 ? 1 : nreq;
@@ -1673,14 +1789,17 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_blend(const Vie
     const View<real> v = nreq == 0 ? single : rebase(views[r], single.base);
     const int cnt = v.bcnt[v.bpar];
     for (int idx = blockIdx.x; idx < cnt; idx += gridDim.x) {
-      surface_body<N, real, 2, LGL, SPLIT>(v, v.blist[idx], mode);
+      int tid = threadIdx.x;
+      asm volatile("" : "+v"(tid));
+      surface_body<N, real, 2, LGL, SPLIT, false, ONE>(v, v.blist[idx], mode, tid);
       __syncthreads();  // LDS is reused by the next listed workgroup
     }
   }
 }
 
-// workgroups of the blend pass: one per CU
-constexpr int kBlendBlocks = 256;
+// workgroups of the blend pass: as many as the GPU holds at once
+template <int N>
+constexpr int kBlendBlocks = Sz<N>::threads <= 256 ? 512 : 256;
 
 // the volume sweep with the viscosity law of the view (a template flag)
 template <int N, typename real, bool SHOCK, bool LGL, bool SPLIT>
@@ -1743,7 +1862,22 @@ static hipError_t launch_nl(Kernel k, int mode, const View<real> *views, const i
       break;
     case K_RHS:
       // surface sweep (after a volume sweep), or the one-sweep Euler operator
-      if (v0.shock) {
+      if (v0.one && v0.shock) {
+        if constexpr (LGL && N >= 2 && N <= 7) {  // what shock capturing accepts
+          if (v0.nt)
+            k_rhs<N, real, true, true, true><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+          else
+            k_rhs<N, real, true, true, false><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+          k_blend<N, real, true, false, true><<<std::min(blocks, kBlendBlocks<N>), block, 0, st>>>(views, nreq, v0, mode);
+        } else {
+          return hipErrorInvalidValue;
+        }
+      } else if (v0.one) {
+        if (v0.nt)
+          k_rhs<N, real, false, LGL, true><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+        else
+          k_rhs<N, real, false, LGL, false><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+      } else if (v0.shock) {
         if constexpr (N >= 2 && N <= 7) {  // the degrees shock capturing accepts
           if (v0.nt)
             k_surface<N, real, 1, LGL, true><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
@@ -1751,23 +1885,21 @@ static hipError_t launch_nl(Kernel k, int mode, const View<real> *views, const i
             k_surface<N, real, 1, LGL, false><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
           if (v0.split) {
             if constexpr (LGL) {
-              k_blend<N, real, LGL, true><<<std::min(blocks, kBlendBlocks), block, 0, st>>>(views, nreq, v0, mode);
+              k_blend<N, real, LGL, true><<<std::min(blocks, kBlendBlocks<N>), block, 0, st>>>(views, nreq, v0, mode);
             } else {
               return hipErrorInvalidValue;
             }
           } else {
-            k_blend<N, real, LGL, false><<<std::min(blocks, kBlendBlocks), block, 0, st>>>(views, nreq, v0, mode);
+            k_blend<N, real, LGL, false><<<std::min(blocks, kBlendBlocks<N>), block, 0, st>>>(views, nreq, v0, mode);
           }
         } else {
           return hipErrorInvalidValue;
         }
-      } else if (v0.viscous || v0.split) {
+      } else {
         if (v0.nt)
           k_surface<N, real, 0, LGL, true><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
         else
           k_surface<N, real, 0, LGL, false><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
-      } else {
-        k_rhs<N, real><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
       }
       break;
     default: return hipErrorInvalidValue;

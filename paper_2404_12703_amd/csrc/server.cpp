@@ -547,12 +547,14 @@ dg_status launch_group(dg_server *sv, Kernel k, int N, const std::vector<Request
 // one RK stage for every active request
 dg_status tick(dg_server *sv) {
   // one group per kernel set: degree, precision, shock capturing, viscosity,
-  // volume form and nodes
+  // viscosity law, sweeps per stage, volume form and nodes
   std::map<std::tuple<int, int, int, int, int>, std::vector<Request *>> groups;
   for (int64_t id : sv->active) {
     Request &r = *sv->reqs[id];
     if (r.retiring || r.step >= r.n_steps) continue;
-    groups[{r.p.N, r.p.precision, r.p.shock_capturing, r.p.viscous, 2 * r.p.volume_flux + r.p.nodes}].push_back(&r);
+    groups[{r.p.N, r.p.precision, r.p.shock_capturing, r.p.viscous,
+            8 * r.p.viscosity_law + 4 * one_sweep(r.p) + 2 * r.p.volume_flux + r.p.nodes}]
+        .push_back(&r);
   }
   if (groups.empty()) return DG_OK;
   hipError_t e = hipEventRecord(sv->fork_ev, sv->st);
@@ -567,7 +569,7 @@ dg_status tick(dg_server *sv) {
     std::vector<Request *> fresh, visc;
     for (Request *r : kv.second) {
       if (!r->traces_valid) fresh.push_back(r);
-      if (r->p.viscous || r->p.shock_capturing || r->p.volume_flux) visc.push_back(r);
+      if (!one_sweep(r->p)) visc.push_back(r);
     }
     dg_status rc;
     rc = mixed ? launch_group<float>(sv, K_TRACE, N, fresh, gs) : launch_group<double>(sv, K_TRACE, N, fresh, gs);

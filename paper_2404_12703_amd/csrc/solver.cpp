@@ -189,6 +189,7 @@ void fill_view(View<real> &v, void *base, const Layout &L, const dg_params &p, i
   v.cpR = (real)(p.gamma * p.R / (p.gamma - 1.0));
   v.Rgas4 = real(4) * (real)p.R;
   v.cpR2 = real(2) * v.cpR;
+  v.one = one_sweep(p);
   v.split = p.volume_flux;
   v.visc_law = p.viscosity_law;
   v.alpha_smooth = p.alpha_smooth;
@@ -379,7 +380,7 @@ static hipError_t stage(dg_solver *s, int mode, double t, double dt, double A, d
     if (e != hipSuccess) return e;
     s->traces_valid = true;
   }
-  if (s->p.viscous || s->p.shock_capturing || s->p.volume_flux) {  // lifting, indicator, split form
+  if (!v.one) {  // lifting, indicator, split form
     e = run_kernel<real>(s, K_LIFT, 0, v);
     if (e != hipSuccess) return e;
   }
