@@ -59,6 +59,8 @@ struct View {
   int cur;          // trace buffer read this stage (0: Utr0, 1: Utr1)
   int bpar;         // entry of bcnt this surface sweep counts in; it clears the other
   int viscous, riemann, source, shock;
+  int affine;       // every element is a parallelepiped (affine_elements): its metrics, 1/J and each
+                    // face's n*shat are the same at every node, and the kernels read the first node's
   int one;          // one sweep per stage (one_sweep): no volume sweep, no stored volume integral
   int split;        // split-form volume integral with Pirozzoli's two-point flux (Gauss-Lobatto)
   int visc_law;     // 0 constant viscosity, 1 Sutherland's law
@@ -125,6 +127,14 @@ struct Geometry {
 // builds metrics, face normals and connectivity; returns DG_OK or DG_EMESH
 // with a message in err.
 int build_geometry(const Basis &b, const dg_mesh &m, Geometry &g, std::string &err);
+
+// Whether every element is a parallelepiped as far as the mesh's coordinates
+// can tell: its metrics and Jacobian vary by no more than rounding the
+// coordinates to double explains.  If so, the metrics of each element are
+// replaced by their mean and the face normals by the primary side's, so that
+// every node of an element holds the same bits and the discrete metric
+// identities stay at round-off.  Otherwise g is unchanged.
+bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g);
 
 // orientation code map (p,q) -> neighbour face coordinates
 __host__ __device__ inline void orient_map(int code, int p, int q, int N, int &pp, int &qq) {

@@ -407,6 +407,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   real *const sf = su + rows;
   const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
   const uint32_t vi = (uint32_t)(e * n3 + a), fb = (uint32_t)(e * 6 * n2);
+  const uint32_t gi = v.affine ? (uint32_t)(e * n3) : vi;  // where this node's metrics stand
   const real gam = v.gamma, rR = v.rRgas;
   const Bg<real> bg{v.bg_p, v.bg_H};
   const real *tr = v.cur ? v.Utr1 : v.Utr0;
@@ -431,7 +432,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
 #pragma unroll
     for (int s = 0; s < 5; ++s) Un[s] = (tr + s * Ef)[in];
 #pragma unroll
-    for (int d = 0; d < 3; ++d) ns[d] = (v.NS + d * Ef)[fb + fn];
+    for (int d = 0; d < 3; ++d) ns[d] = (v.NS + d * Ef)[fb + (v.affine ? f * n2 : fn)];
   };
   if (active) {
 #pragma unroll
@@ -441,7 +442,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
     // spilled at N = 4
     if (a < nf) fetch(a);
 #pragma unroll
-    for (int c = 0; c < 9; ++c) Ja[c] = ld<NT>(v.Ja + c * Ev + vi);
+    for (int c = 0; c < 9; ++c) Ja[c] = ld<NT>(v.Ja + c * Ev + gi);
 #pragma unroll
     for (int c = 0; c < 5; ++c) su[c * Pad<n>::size + pa] = to_real(Uold[c], c, v);
   }
@@ -540,7 +541,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
 #pragma unroll
     for (int c = 0; c < 5; ++c) U[c] = to_real(Uold[c], c, v);
     cons2prim(U, gam, rR, P, bg);
-    iJ = v.invJ[vi];
+    iJ = v.invJ[gi];
 #pragma unroll
     for (int c = 0; c < 5; ++c) dUo[c] = (mode == 0 && v.rkA != 0.0) ? ld<NT>(v.dU + c * Ev + vi) : 0.0;
     flux_adv<0>(U, P, Fx, bg);
@@ -734,6 +735,45 @@ __device__ __forceinline__ void fv_subcells(real *rows, const real *sFV, bool ac
   }
 }
 
+// ---------------------------------------------------------------------------
+// The xi and eta contractions with D-hat of one row of node values, at N = 7
+// in FP64, on the 4x4x4 four-block matrix instruction.  Its operands sit at
+// A[m][k]: lane 16k + 4b + m, B[k][n]: lane 16k + 4b + n, and its result at
+// D[m][n]: lane 16m + 4b + n.  A wave holds one k-plane with node (i, j) on
+// lane i + 8j, so taking i = n + 4 (b & 1) and j = (b >> 1) + 2m as the output
+// indices puts every result in the lane that owns the node.  xi: A = values
+// (row j, source l), B = D-hat^T; eta: A = D-hat (row j), B = values (column i,
+// source l); sources in two halves of four.  Each lane reads each value it
+// feeds once, where the per-lane sums read it eight times.
+// ---------------------------------------------------------------------------
+struct PlaneMfma {
+  int lk, ix, jx;
+  double bx[2], ay[2];
+  __device__ __forceinline__ explicit PlaneMfma(const double *Dh) {
+    const int lane = threadIdx.x & 63;
+    lk = lane >> 4;
+    ix = lane & 7;
+    jx = ((lane >> 3) & 1) + 2 * (lane & 3);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      bx[h] = Dh[ix * 9 + 4 * h + lk];
+      ay[h] = Dh[jx * 9 + 4 * h + lk];
+    }
+  }
+  __device__ __forceinline__ double xi(const double *plane, double acc) const {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      acc = __builtin_amdgcn_mfma_f64_4x4x4f64(plane[vnode(8, 4 * h + lk, jx, 0)], bx[h], acc, 0, 0, 0);
+    return acc;
+  }
+  __device__ __forceinline__ double eta(const double *plane, double acc) const {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      acc = __builtin_amdgcn_mfma_f64_4x4x4f64(ay[h], plane[vnode(8, ix, 4 * h + lk, 0)], acc, 0, 0, 0);
+    return acc;
+  }
+};
+
 // Face work unit t of an element: the direction d and first side s0 of its
 // face nodes and their face index pq.  fpu = 2: both sides of line pq; fpu = 1:
 // face node t.  With plane waves each wave's units share one face direction.
@@ -854,6 +894,7 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
   // (the host keeps every row below 2^31 entries)
   const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
   const uint32_t vi = (uint32_t)(e * n3 + a), fb = (uint32_t)(e * 6 * n2);
+  const uint32_t gi = v.affine ? (uint32_t)(e * n3) : vi, gstep = v.affine ? 0 : tpe;  // where the metrics stand
   const real gam = v.gamma, rR = v.rRgas, mu = v.mu, lam = v.lambda;
   const Bg<real> bg{v.bg_p, v.bg_H};
   const bool visc = v.viscous != 0;  // the same for the whole grid
@@ -888,7 +929,7 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
   real iJe[npt];
   if (active && visc) {
 #pragma unroll
-    for (int m = 0; m < npt; ++m) iJe[m] = v.invJ[vi + m * tpe];
+    for (int m = 0; m < npt; ++m) iJe[m] = v.invJ[gi + m * gstep];
   }
   // Lift_FillFlux operands: both sides' U traces and this side's n shat at
   // the thread's face nodes.  With one node per thread they are fetched here,
@@ -909,7 +950,7 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
       tUn[r][u][s] = (tr + s * Ef)[in];
     }
 #pragma unroll
-    for (int dd = 0; dd < 3; ++dd) tNs[r][u][dd] = (v.NS + dd * Ef)[io];
+    for (int dd = 0; dd < 3; ++dd) tNs[r][u][dd] = (v.NS + dd * Ef)[v.affine ? fb + f * n2 : io];
   };
   if (npt == 1 && active && visc) {
 #pragma unroll
@@ -945,7 +986,7 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
     for (int m = 0; m < npt; ++m) {
       const int am = a + m * tpe;
 #pragma unroll
-      for (int c = 0; c < 9; ++c) sm[L::J + c * n3 + am] = ld<NT>(v.Ja + c * Ev + vi + m * tpe);
+      for (int c = 0; c < 9; ++c) sm[L::J + c * n3 + am] = ld<NT>(v.Ja + c * Ev + gi + m * gstep);
       real P[6];
       cons2prim(U[m], gam, rR, P, bg);
       sm[L::V + 0 * n3 + am] = P[1];
@@ -1170,7 +1211,7 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
       const real *gm = g[m];
       const double T = (double)sm[L::V + 3 * n3 + a + m * tpe];
       const double mud = v.visc_law ? sutherland<double>(T, (double)mu, (double)v.rTref) : (double)mu;
-      const double wJ = (double)wq[i] * (double)wq[j] * (double)wq[k0 + m * kstep] / (double)v.invJ[vi + m * tpe];
+      const double wJ = (double)wq[i] * (double)wq[j] * (double)wq[k0 + m * kstep] / (double)v.invJ[gi + m * gstep];
       const double wx = (double)gm[1 * 4 + 2] - (double)gm[2 * 4 + 1];
       const double wy = (double)gm[2 * 4 + 0] - (double)gm[0 * 4 + 2];
       const double wz = (double)gm[0 * 4 + 1] - (double)gm[1 * 4 + 0];
@@ -1326,53 +1367,31 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
     for (int m = 0; m < npt; ++m)
 #pragma unroll
       for (int c = 0; c < 5; ++c) Vi[m][c] = real(0);
-    if (contract && L::mfma) {
-      // xi and eta on the FP64 4x4x4 four-block matrix instruction.  Its
-      // operands sit at A[m][k]: lane 16k + 4b + m, B[k][n]: lane 16k + 4b + n,
-      // and its result at D[m][n]: lane 16m + 4b + n.  A wave holds one
-      // k-plane (with column pairs also the plane n/2 above) with node (i, j)
-      // on lane i + 8j, so taking i = n + 4 (b & 1) and
-      // j = (b >> 1) + 2m as the output indices puts every result in the lane
-      // that owns the node.  xi: A = fluxes (row j, source l), B = D-hat^T;
-      // eta: A = D-hat (row j), B = fluxes (column i, source l); sources in
-      // two halves of four.  Each lane reads each flux value it feeds once.
-      const int lane = threadIdx.x & 63, lk = lane >> 4;
-      const int ix = lane & 7, jx = ((lane >> 3) & 1) + 2 * (lane & 3);
-      double bx[2], ay[2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        bx[h] = sb.Dh[ix * (n + 1) + 4 * h + lk];
-        ay[h] = sb.Dh[jx * (n + 1) + 4 * h + lk];
-      }
-#pragma unroll
-      for (int m = 0; m < npt; ++m) {
-        const int km = k0 + m * kstep;
-#pragma unroll
-        for (int c = c0; c < 5; ++c) {
-          double acc = 0.0;
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            acc = __builtin_amdgcn_mfma_f64_4x4x4f64(sm[L::F + c * n3 + vnode(n, 4 * h + lk, jx, km)], bx[h], acc, 0,
-                                                     0, 0);
-#pragma unroll
-          for (int h = 0; h < 2; ++h)
-            acc = __builtin_amdgcn_mfma_f64_4x4x4f64(ay[h], sm[L::F + (5 + c) * n3 + vnode(n, ix, 4 * h + lk, km)],
-                                                     acc, 0, 0, 0);
-          Vi[m][c] = acc;
-        }
-      }
-      // zeta along the thread's own column
-#pragma unroll
-      for (int alp = 0; alp < n; ++alp) {
-        const int src = vnode(n, i, j, alp);
-        real fz[5];
-#pragma unroll
-        for (int c = c0; c < 5; ++c) fz[c] = sm[L::F + (10 + c) * n3 + src];
+    if constexpr (L::mfma) {
+      if (contract) {
+        const PlaneMfma M(sb.Dh);
 #pragma unroll
         for (int m = 0; m < npt; ++m) {
-          const real dh = plane_waves ? dk[m][alp] : sb.Dh[(k0 + m * kstep) * (n + 1) + alp];
+          const int km = k0 + m * kstep;
 #pragma unroll
-          for (int c = c0; c < 5; ++c) Vi[m][c] += dh * fz[c];
+          for (int c = c0; c < 5; ++c) {
+            Vi[m][c] = M.xi(sm + L::F + c * n3 + n2 * km, 0.0);
+            Vi[m][c] = M.eta(sm + L::F + (5 + c) * n3 + n2 * km, Vi[m][c]);
+          }
+        }
+        // zeta along the thread's own column
+#pragma unroll
+        for (int alp = 0; alp < n; ++alp) {
+          const int src = vnode(n, i, j, alp);
+          real fz[5];
+#pragma unroll
+          for (int c = c0; c < 5; ++c) fz[c] = sm[L::F + (10 + c) * n3 + src];
+#pragma unroll
+          for (int m = 0; m < npt; ++m) {
+            const real dh = plane_waves ? dk[m][alp] : sb.Dh[(k0 + m * kstep) * (n + 1) + alp];
+#pragma unroll
+            for (int c = c0; c < 5; ++c) Vi[m][c] += dh * fz[c];
+          }
         }
       }
     } else if (contract) {
@@ -1443,6 +1462,328 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
   }
 }
 
+template <int N, typename real>
+struct AffLds {
+  using S = Sz<N>;
+  static constexpr int n3 = S::n3, nf = S::nf;
+  // lifting: u, v, w, T (4 rows of n3) and the BR1 face averages (4 x nf);
+  // then g (12 padded rows), then the 15 rows of contravariant fluxes
+  static constexpr int V = 0, Avg = 4 * n3, G = 0, F = 0, gsz = Pad<S::n>::size;
+  static constexpr int m1 = 4 * n3 + 4 * nf, m2 = 12 * gsz, m3 = 15 * n3;
+  static constexpr int rows = m1 > m2 ? (m1 > m3 ? m1 : m3) : (m2 > m3 ? m2 : m3);
+  static constexpr bool plane_waves = S::n2 == 64 && S::epb == 1;
+  static constexpr bool mfma = sizeof(real) == 8 && N == 7;
+  // face nodes per work unit: as in VolLds, but one at N = 7 in the mixed form
+  // (194 against 205 us on 24^3; in FP64 one took 110 against 106 us on 16^3,
+  // at N = 3 122 against 106 on 30^3; two took 302 against 239 us at N = 6 on
+  // 20^3 and 142 against 132 at N = 9 on 12^3, and at N = 5 the same)
+  static constexpr int fpu = (N == 7 && sizeof(real) == 4) ? 1 : VolLds<N, real, false, false>::fpu;
+  static constexpr int units = nf / fpu, upt = (units + n3 - 1) / n3;
+};
+
+// ---------------------------------------------------------------------------
+// Volume sweep of the viscous standard form without shock capturing on a mesh
+// of parallelepipeds (View::affine): the same result as k_volume up to
+// round-off.  The metrics are nine numbers per element, so they come out of
+// the contractions: the lifting differentiates u, v, w, T along each
+// direction (12 sums per source node instead of 36 products and 36 sums) and
+// applies the metrics once per node, and the nine metric rows and the face
+// normals take neither HBM traffic (98 of 262 bytes per node at N = 7) nor
+// LDS.  16^3 at N = 7: 139 -> 104 us (3.3 TB/s; its LDS accesses and its FP64
+// arithmetic take about 40 us each, which 16 waves per CU overlap in part).
+// The contravariant fluxes formed after the face phase instead of held
+// through it (116 against 124 VGPRs) measured 2% slower.
+// ---------------------------------------------------------------------------
+template <int N, typename real, bool LGL, bool SUTH, bool NT>
+__global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_volume_affine(const View<real> *views,
+                                                                                const int *blk_start, int nreq,
+                                                                                View<real> single) {
+  using S = Sz<N>;
+  using L = AffLds<N, real>;
+  constexpr int n = S::n, n2 = S::n2, n3 = S::n3, nf = S::nf, epb = S::epb;
+  int lblk;
+  const View<real> v = select_view(views, blk_start, nreq, single, lblk);
+  __shared__ Smem<N, real> sb;
+  __shared__ __align__(16) real sA[epb][L::rows];
+  load_basis<N, real>(sb, v.basis, threadIdx.x);
+  const int le = threadIdx.x / n3, a = threadIdx.x - le * n3;
+  const int64_t e = (int64_t)lblk * epb + le;
+  const bool active = le < epb && e < v.E;
+  real *const sm = sA[le < epb ? le : 0];
+  const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
+  const uint32_t vi = (uint32_t)(e * n3 + a), fb = (uint32_t)(e * 6 * n2);
+  // the element's metrics: scalar loads where a workgroup holds one element
+  const int64_t em = epb == 1 ? (int64_t)lblk : (active ? e : 0);
+  const real gam = v.gamma, rR = v.rRgas, mu = v.mu, lam = v.lambda;
+  const Bg<real> bg{v.bg_p, v.bg_H};
+  const real *tr = v.cur ? v.Utr1 : v.Utr0;
+  const int i = a % n, j = (a / n) % n, k = a / n2;
+  constexpr bool plane_waves = L::plane_waves;
+  real dk[n];  // row k of D-hat: wave-uniform when a wave is one k-plane
+  if constexpr (plane_waves) {
+    const int ku = __builtin_amdgcn_readfirstlane(k);
+    const BasisOffsets o(n);
+#pragma unroll
+    for (int al = 0; al < n; ++al) dk[al] = v.basis[o.Dhat + ku * n + al];
+  }
+  real U[5], pf[L::upt][L::fpu][4];
+  bool prim[L::upt][L::fpu];
+  real tUo[L::fpu][5], tUn[L::fpu][5];
+  // both sides' traces at the face nodes of work unit t = a + r n3
+  auto fetch = [&](int r, int d, int s0, int pq) {
+#pragma unroll
+    for (int u = 0; u < L::fpu; ++u) {
+      const int f = 2 * d + s0 + u;
+      const int2 c = v.conn[e * 6 + f];
+      prim[r][u] = (c.y >> 3) & 1;
+      int pp, qq;
+      orient_map(c.y & 7, pq % n, pq / n, N, pp, qq);
+      const uint32_t io = fb + f * n2 + pq, in = (uint32_t)c.x * n2 + pp + n * qq;
+#pragma unroll
+      for (int s = 0; s < 5; ++s) {
+        tUo[u][s] = (tr + s * Ef)[io];
+        tUn[u][s] = (tr + s * Ef)[in];
+      }
+    }
+  };
+  if (active) {
+#pragma unroll
+    for (int c = 0; c < 5; ++c) U[c] = to_real(ld<NT>(v.U + c * Ev + vi), c, v);
+    // the first unit's traces beside the state (a second one's, at N = 1,
+    // where it is used: held from here they spilled)
+    if (a < L::units) {
+      int d, s0, pq;
+      face_unit<n, L::fpu, plane_waves>(a, d, s0, pq);
+      fetch(0, d, s0, pq);
+    }
+  }
+  real Ja[9];
+#pragma unroll
+  for (int c = 0; c < 9; ++c) Ja[c] = (v.Ja + c * Ev)[em * n3];
+  const real iJ = v.invJ[em * n3];
+  real mun = mu;
+  if (active) {
+    real P[6];
+    cons2prim(U, gam, rR, P, bg);
+    sm[L::V + a] = P[1];
+    sm[L::V + n3 + a] = P[2];
+    sm[L::V + 2 * n3 + a] = P[3];
+    sm[L::V + 3 * n3 + a] = P[5];
+    if (SUTH) mun = sutherland(P[5], mu, v.rTref);
+    // Lift_FillFlux: the BR1 average of both sides' traces
+#pragma unroll
+    for (int r = 0; r < L::upt; ++r) {
+      const int t = a + r * n3;
+      if (t < L::units) {
+        int d, s0, pq;
+        face_unit<n, L::fpu, plane_waves>(t, d, s0, pq);
+        if (r > 0) fetch(r, d, s0, pq);
+#pragma unroll
+        for (int u = 0; u < L::fpu; ++u) {
+          const int fn = (2 * d + s0 + u) * n2 + pq;
+          real Po[6], Pn[6];
+          cons2prim(tUo[u], gam, rR, Po, bg);
+          cons2prim(tUn[u], gam, rR, Pn, bg);
+          const real vo[4] = {Po[1], Po[2], Po[3], Po[5]}, vn[4] = {Pn[1], Pn[2], Pn[3], Pn[5]};
+#pragma unroll
+          for (int s = 0; s < 4; ++s) sm[L::Avg + s * nf + fn] = real(0.5) * (vo[s] + vn[s]);
+#pragma unroll
+          for (int dd = 0; dd < 3; ++dd) pf[r][u][dd] = Po[1 + dd];
+          pf[r][u][3] = SUTH ? sutherland(Po[5], mu, v.rTref) : mu;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  real g[12];
+  if (active) {
+    // Lift_VolInt and Lift_SurfInt of u, v, w, T along the three directions
+    // (n shat of the faces of direction i is -+ Ja^i), then the metrics
+    real w[3][4];
+    if constexpr (L::mfma) {
+      const PlaneMfma M(sb.Dh);
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const real *plane = sm + L::V + s * n3 + n2 * k;
+        w[0][s] = M.xi(plane, 0.0);
+        w[1][s] = M.eta(plane, 0.0);
+      }
+    } else {
+#pragma unroll
+      for (int ci = 0; ci < 2; ++ci) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) w[ci][s] = real(0);
+#pragma unroll
+        for (int al = 0; al < n; ++al) {
+          const int src = ci == 0 ? vnode(n, al, j, k) : vnode(n, i, al, k);
+          const real dh = sb.Dh[(ci == 0 ? i : j) * (n + 1) + al];
+#pragma unroll
+          for (int s = 0; s < 4; ++s) w[ci][s] += dh * sm[L::V + s * n3 + src];
+        }
+      }
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) w[2][s] = real(0);
+#pragma unroll
+    for (int al = 0; al < n; ++al) {
+      const real dh = plane_waves ? dk[al] : sb.Dh[k * (n + 1) + al];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) w[2][s] += dh * sm[L::V + s * n3 + vnode(n, i, j, al)];
+    }
+    const int lf[3] = {i, j, k};
+    const int pqf[3] = {j + n * k, i + n * k, i + n * j};
+#pragma unroll
+    for (int f = 0; f < 6; ++f) {
+      const int d = f >> 1;
+      if (LGL && lf[d] != ((f & 1) ? n - 1 : 0)) continue;  // l-hat vanishes off the end nodes
+      const real lh = (f & 1) ? sb.lhp[lf[d]] : -sb.lhm[lf[d]];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) w[d][s] += lh * sm[L::Avg + s * nf + f * n2 + pqf[d]];
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) g[d * 4 + s] = iJ * (Ja[d] * w[0][s] + Ja[3 + d] * w[1][s] + Ja[6 + d] * w[2][s]);
+    }
+  }
+  real Fc[15];  // contravariant fluxes Ja^i . (F_adv - F_v)
+  if (active) {
+    real P[6];
+    cons2prim(U, gam, rR, P, bg);
+    const real lamn = SUTH ? mun * v.kappa : lam;
+    real Fx[5], Fy[5], Fz[5], Vx[5], Vy[5], Vz[5];
+    flux_adv<0>(U, P, Fx, bg);
+    flux_adv<1>(U, P, Fy, bg);
+    flux_adv<2>(U, P, Fz, bg);
+    flux_visc<0>(P, g, mun, lamn, Vx);
+    flux_visc<1>(P, g, mun, lamn, Vy);
+    flux_visc<2>(P, g, mun, lamn, Vz);
+#pragma unroll
+    for (int c = 0; c < 5; ++c) {
+      Fx[c] -= Vx[c];
+      Fy[c] -= Vy[c];
+      Fz[c] -= Vz[c];
+    }
+#pragma unroll
+    for (int ci = 0; ci < 3; ++ci)
+#pragma unroll
+      for (int c = 0; c < 5; ++c) Fc[5 * ci + c] = Ja[3 * ci] * Fx[c] + Ja[3 * ci + 1] * Fy[c] + Ja[3 * ci + 2] * Fz[c];
+  }
+  __syncthreads();  // the rows read above are covered by g
+  if (active) {
+    const int pa = Pad<n>::at(i, j, k);
+#pragma unroll
+    for (int c = 0; c < 12; ++c) sm[L::G + c * L::gsz + pa] = g[c];
+  }
+  __syncthreads();
+  if (active) {
+    // Lift_ProlongToFace of g, then this side's viscous normal flux
+#pragma unroll
+    for (int r = 0; r < L::upt; ++r) {
+      const int t = a + r * n3;
+      if (t < L::units) {
+        int d, s0, pq;
+        face_unit<n, L::fpu, plane_waves>(t, d, s0, pq);
+        int base, stride;
+        Pad<n>::face_line(2 * d, pq, base, stride);
+        const BasisOffsets o(n);
+        const real *lw[L::fpu];
+#pragma unroll
+        for (int u = 0; u < L::fpu; ++u) {
+          const bool plus = (s0 + u) != 0;
+          lw[u] = plane_waves ? v.basis + (plus ? o.lp : o.lm) : (plus ? sb.lp : sb.lm);
+        }
+        real gt[L::fpu][12];
+        if constexpr (LGL) {
+#pragma unroll
+          for (int u = 0; u < L::fpu; ++u) {
+            const real *row = sm + L::G + base + ((s0 + u) != 0 ? (n - 1) * stride : 0);
+#pragma unroll
+            for (int s = 0; s < 12; ++s) gt[u][s] = row[s * L::gsz];
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < L::fpu; ++u)
+#pragma unroll
+            for (int s = 0; s < 12; ++s) gt[u][s] = real(0);
+#pragma unroll
+          for (int l = 0; l < n; ++l) {
+            const real *row = sm + L::G + base + l * stride;
+#pragma unroll
+            for (int s = 0; s < 12; ++s) {
+              const real gv = row[s * L::gsz];
+#pragma unroll
+              for (int u = 0; u < L::fpu; ++u) gt[u][s] += lw[u][l] * gv;
+            }
+          }
+        }
+        // the unit normal in the primary side's orientation: -+ Ja^d / |Ja^d|
+        const real m0 = d == 0 ? Ja[0] : (d == 1 ? Ja[3] : Ja[6]);
+        const real m1 = d == 0 ? Ja[1] : (d == 1 ? Ja[4] : Ja[7]);
+        const real m2 = d == 0 ? Ja[2] : (d == 1 ? Ja[5] : Ja[8]);
+        const real im = real(1) / sqrt(m0 * m0 + m1 * m1 + m2 * m2);
+#pragma unroll
+        for (int u = 0; u < L::fpu; ++u) {
+          const int fn = (2 * d + s0 + u) * n2 + pq;
+          const real sg = ((s0 + u) != 0) == prim[r][u] ? im : -im;
+          const real nv[3] = {m0 * sg, m1 * sg, m2 * sg};
+          const real Pf[6] = {real(0), pf[r][u][0], pf[r][u][1], pf[r][u][2], real(0), real(0)};
+          const real muf = pf[r][u][3];
+          const real lamf = SUTH ? muf * v.kappa : lam;
+          real H[5] = {0, 0, 0, 0, 0}, tmp[5];
+          flux_visc<0>(Pf, gt[u], muf, lamf, tmp);
+#pragma unroll
+          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[0];
+          flux_visc<1>(Pf, gt[u], muf, lamf, tmp);
+#pragma unroll
+          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[1];
+          flux_visc<2>(Pf, gt[u], muf, lamf, tmp);
+#pragma unroll
+          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[2];
+#pragma unroll
+          for (int s = 1; s < 5; ++s) st<NT>(H[s], v.Hv + (s - 1) * Ef + fb + fn);
+        }
+      }
+    }
+  }
+  __syncthreads();  // g is read above; the flux rows cover it
+  if (active) {
+#pragma unroll
+    for (int c = 0; c < 15; ++c) sm[L::F + c * n3 + a] = Fc[c];
+  }
+  __syncthreads();
+  if (active) {
+    // VolInt
+    real Vi[5] = {0, 0, 0, 0, 0};
+    if constexpr (L::mfma) {
+      const PlaneMfma M(sb.Dh);
+#pragma unroll
+      for (int c = 0; c < 5; ++c) {
+        Vi[c] = M.xi(sm + L::F + c * n3 + n2 * k, 0.0);
+        Vi[c] = M.eta(sm + L::F + (5 + c) * n3 + n2 * k, Vi[c]);
+      }
+    } else {
+#pragma unroll
+      for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+        for (int al = 0; al < n; ++al) {
+          const int src = ci == 0 ? vnode(n, al, j, k) : vnode(n, i, al, k);
+          const real dh = sb.Dh[(ci == 0 ? i : j) * (n + 1) + al];
+#pragma unroll
+          for (int c = 0; c < 5; ++c) Vi[c] += dh * sm[L::F + (5 * ci + c) * n3 + src];
+        }
+    }
+#pragma unroll
+    for (int al = 0; al < n; ++al) {
+      const real dh = plane_waves ? dk[al] : sb.Dh[k * (n + 1) + al];
+#pragma unroll
+      for (int c = 0; c < 5; ++c) Vi[c] += dh * sm[L::F + (10 + c) * n3 + vnode(n, i, j, al)];
+    }
+#pragma unroll
+    for (int c = 0; c < 5; ++c) st<NT>(Vi[c], v.Vol + c * Ev + vi);
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Surface sweep of one workgroup of elements: FillFlux from this side's
 // recomputed U trace, the neighbour's stored one and the mean of both sides'
@@ -1490,6 +1831,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
   const bool active = le < epb && e < v.E;
   const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
   const uint32_t vi = (uint32_t)(e * n3 + a), fb = (uint32_t)(e * 6 * n2);
+  const uint32_t gi = v.affine ? (uint32_t)(e * n3) : vi;  // where this node's metrics stand
   const real gam = v.gamma, rR = v.rRgas;
   const Bg<real> bg{v.bg_p, v.bg_H};
   const bool visc = v.viscous != 0;  // the same for the whole grid
@@ -1584,7 +1926,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
       real nsv[3];
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        const real ns = (v.NS + d * Ef)[io];
+        const real ns = (v.NS + d * Ef)[v.affine ? fb + f * n2 : io];
         nsv[d] = primary ? ns : -ns;
       }
       const real sh = sqrt(nsv[0] * nsv[0] + nsv[1] * nsv[1] + nsv[2] * nsv[2]);
@@ -1619,7 +1961,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
         for (int c = 0; c < 5; ++c) U[c] = to_real(Uold[c], c, v);
         cons2prim(U, gam, rR, P, bg);
 #pragma unroll
-        for (int c = 0; c < 9; ++c) Ja[c] = (v.Ja + c * Ev)[vi];
+        for (int c = 0; c < 9; ++c) Ja[c] = (v.Ja + c * Ev)[gi];
       }
       real Vfv[5] = {0, 0, 0, 0, 0};
       fv_subcells<N, real>(rows, sFV, active, a, i, j, k, P, Ja, gam, rR, bg, Vfv);
@@ -1691,7 +2033,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
     // 1/J and the RK register, loaded with the volume integral: their latency
     // overlaps the gather, and the register's five loads precede its five
     // stores (which the compiler could not move them across)
-    const real iJ = v.invJ[vi];
+    const real iJ = v.invJ[gi];
     double dUo[5];
 #pragma unroll
     for (int c = 0; c < 5; ++c) dUo[c] = (mode == 0 && v.rkA != 0.0) ? ld<NT>(v.dU + c * Ev + vi) : 0.0;
@@ -1806,6 +2148,20 @@ template <int N, typename real, bool SHOCK, bool LGL, bool SPLIT>
 static void volume_sweep(dim3 grid, const View<real> *views, const int *blk_start, int nreq, const View<real> &v0,
                          hipStream_t st) {
   constexpr int threads = VolLds<N, real, SHOCK, SPLIT>::threads;
+  if constexpr (!SHOCK && !SPLIT) {
+    // a mesh of parallelepipeds
+    if (v0.affine && v0.viscous) {
+      const int at = Sz<N>::threads;
+      if (v0.nt) {
+        if (v0.visc_law) k_volume_affine<N, real, LGL, true, true><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
+        else k_volume_affine<N, real, LGL, false, true><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
+      } else {
+        if (v0.visc_law) k_volume_affine<N, real, LGL, true, false><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
+        else k_volume_affine<N, real, LGL, false, false><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
+      }
+      return;
+    }
+  }
   if (v0.nt) {
     if (v0.visc_law)
       k_volume<N, real, SHOCK, LGL, SPLIT, true, false, true><<<grid, threads, 0, st>>>(views, blk_start, nreq, v0);

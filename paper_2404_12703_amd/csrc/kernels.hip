@@ -29,13 +29,14 @@ __global__ void __launch_bounds__(256) k_dt(View<real> v, double *out) {
     for (int c = 0; c < 5; ++c) U[c] = v.U[((int64_t)c * v.E + e) * n3 + a];
     cons2prim(U, gam, (double)v.rRgas, P);
     const double c = sqrt(gam * P[4] / P[0]);
-    const double iJ = (double)v.invJ[e * n3 + a];
+    const int ga = v.affine ? 0 : a;  // where this node's metrics stand
+    const double iJ = (double)v.invJ[e * n3 + ga];
     double lamsum = 0.0, vis = 0.0;
 #pragma unroll
     for (int ci = 0; ci < 3; ++ci) {
-      const double j0 = v.Ja[((int64_t)(3 * ci) * v.E + e) * n3 + a];
-      const double j1 = v.Ja[((int64_t)(3 * ci + 1) * v.E + e) * n3 + a];
-      const double j2 = v.Ja[((int64_t)(3 * ci + 2) * v.E + e) * n3 + a];
+      const double j0 = v.Ja[((int64_t)(3 * ci) * v.E + e) * n3 + ga];
+      const double j1 = v.Ja[((int64_t)(3 * ci + 1) * v.E + e) * n3 + ga];
+      const double j2 = v.Ja[((int64_t)(3 * ci + 2) * v.E + e) * n3 + ga];
       const double nj = sqrt(j0 * j0 + j1 * j1 + j2 * j2);
       lamsum += (fabs(P[1] * j0 + P[2] * j1 + P[3] * j2) + c * nj) * iJ;
       vis += (nj * iJ) * (nj * iJ);
@@ -77,7 +78,7 @@ __global__ void __launch_bounds__(256) k_integrals(View<real> v, double *out) {
     const int64_t e = t / n3;
     const int a = (int)(t - e * n3);
     const int i = a % n, j = (a / n) % n, k = a / n2;
-    const double wJ = sw[i] * sw[j] * sw[k] / (double)v.invJ[e * n3 + a];
+    const double wJ = sw[i] * sw[j] * sw[k] / (double)v.invJ[e * n3 + (v.affine ? 0 : a)];
     double U[5];
 #pragma unroll
     for (int c = 0; c < 5; ++c) {

@@ -430,6 +430,7 @@ dg_status admit(dg_server *sv) {
     fill_view(r.vf, base, r.L, r.p, r.E);
     attach_geometry(r.vd, sv->arena + git->second.off, r.Lg);
     attach_geometry(r.vf, sv->arena + git->second.off, r.Lg);
+    r.vd.affine = r.vf.affine = r.host->affine;
     if (e == hipSuccess) e = hipMemsetAsync(base, 0, r.L.total, sv->cst);
     if (e == hipSuccess) {
       const void *src = r.up_off != SIZE_MAX ? (const void *)(sv->up_host + r.up_off) : (const void *)r.U0.data();
@@ -547,13 +548,13 @@ dg_status launch_group(dg_server *sv, Kernel k, int N, const std::vector<Request
 // one RK stage for every active request
 dg_status tick(dg_server *sv) {
   // one group per kernel set: degree, precision, shock capturing, viscosity,
-  // viscosity law, sweeps per stage, volume form and nodes
+  // parallelepiped meshes, viscosity law, sweeps per stage, volume form and nodes
   std::map<std::tuple<int, int, int, int, int>, std::vector<Request *>> groups;
   for (int64_t id : sv->active) {
     Request &r = *sv->reqs[id];
     if (r.retiring || r.step >= r.n_steps) continue;
     groups[{r.p.N, r.p.precision, r.p.shock_capturing, r.p.viscous,
-            8 * r.p.viscosity_law + 4 * one_sweep(r.p) + 2 * r.p.volume_flux + r.p.nodes}]
+            16 * r.vd.affine + 8 * r.p.viscosity_law + 4 * one_sweep(r.p) + 2 * r.p.volume_flux + r.p.nodes}]
         .push_back(&r);
   }
   if (groups.empty()) return DG_OK;

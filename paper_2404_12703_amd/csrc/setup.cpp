@@ -9,6 +9,7 @@
 //   Sec. 2.2 "Mapping the Equations": Ja^i_n = -e_i . curl_xi(x_l grad_xi x_m).
 //   Sec. 2.3: subcell interfaces at the cumulative Lobatto weights.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdio>
 #include <thread>
@@ -448,6 +449,63 @@ int build_geometry(const Basis &b, const dg_mesh &m, Geometry &g, std::string &e
       }
     }
   return DG_OK;
+}
+
+bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
+  const int n = b.n, n2 = n * n, n3 = n2 * n;
+  const int64_t E = m.n_elems;
+  const int ng = m.n_geo + 1, ng3 = ng * ng * ng;
+  auto ja = [&](int c, int64_t e) { return g.Ja.data() + ((size_t)c * E + e) * n3; };
+  std::vector<double> mean((size_t)9 * E), meanJ(E);
+  double xmax = 0.0;
+  for (size_t t = 0; t < (size_t)E * 3 * ng3; ++t) xmax = std::max(xmax, std::fabs(m.x_geo[t]));
+  std::atomic<bool> affine{true};
+  parallel_for(E, [&](int64_t e) {
+    if (!affine.load(std::memory_order_relaxed)) return;
+    auto average = [&](const double *x) {
+      xr s = 0;
+      for (int a = 0; a < n3; ++a) s += x[a];
+      return (double)(s / n3);
+    };
+    auto spread = [&](const double *x, double mid) {
+      double s = 0.0;
+      for (int a = 0; a < n3; ++a) s = std::max(s, std::fabs(x[a] - mid));
+      return s;
+    };
+    const double J = average(g.J.data() + (size_t)e * n3);
+    double size[3], M[9], off = 0.0;
+    for (int c = 0; c < 9; ++c) {
+      M[c] = average(ja(c, e));
+      mean[(size_t)c * E + e] = M[c];
+    }
+    for (int i = 0; i < 3; ++i) size[i] = std::sqrt(M[3 * i] * M[3 * i] + M[3 * i + 1] * M[3 * i + 1] + M[3 * i + 2] * M[3 * i + 2]);
+    const double big = std::max(size[0], std::max(size[1], size[2]));
+    for (int c = 0; c < 9; ++c) off = std::max(off, spread(ja(c, e), M[c]));
+    // a coordinate is rounded by eps x / 2, x the mesh's extent; the curl form
+    // differentiates twice (entries up to n_geo^2 / 2 each) and its leading
+    // terms cancel: measured on boxes and sheared boxes up to 0.9 n_geo^3 eps x/h
+    // of the largest metric.  2 J / |Ja^i| is the element's width h along i
+    const double tol = 2.3e-16 * std::max(1.0, xmax * big / (2.0 * J)) * 2.0 * m.n_geo * m.n_geo * m.n_geo + 1e-15;
+    if (off > tol * big || spread(g.J.data() + (size_t)e * n3, J) > 3.0 * tol * J) affine.store(false);
+    meanJ[e] = J;
+  });
+  if (!affine.load()) return false;
+  parallel_for(E, [&](int64_t e) {
+    for (int c = 0; c < 9; ++c) std::fill(g.Ja.begin() + ((size_t)c * E + e) * n3, g.Ja.begin() + ((size_t)c * E + e + 1) * n3, mean[(size_t)c * E + e]);
+    std::fill(g.J.begin() + (size_t)e * n3, g.J.begin() + (size_t)(e + 1) * n3, meanJ[e]);
+    for (int f = 0; f < 6; ++f) {
+      const int2 cn = g.conn[e * 6 + f];
+      const bool primary = (cn.y >> 3) & 1;
+      const int64_t pe = primary ? e : cn.x / 6;
+      const int pf = primary ? f : cn.x % 6;
+      const double sg = ((pf & 1) ? 1.0 : -1.0) * (primary ? 1.0 : -1.0);
+      for (int c = 0; c < 3; ++c) {
+        auto at = g.NS.begin() + ((size_t)c * E * 6 + e * 6 + f) * n2;
+        std::fill(at, at + n2, sg * mean[(size_t)(3 * (pf / 2) + c) * E + pe]);
+      }
+    }
+  });
+  return true;
 }
 
 }  // namespace dg

@@ -189,6 +189,7 @@ void fill_view(View<real> &v, void *base, const Layout &L, const dg_params &p, i
   v.cpR = (real)(p.gamma * p.R / (p.gamma - 1.0));
   v.Rgas4 = real(4) * (real)p.R;
   v.cpR2 = real(2) * v.cpR;
+  v.affine = 0;  // known once the geometry is (HostSetup::affine)
   v.one = one_sweep(p);
   v.split = p.volume_flux;
   v.visc_law = p.viscosity_law;
@@ -224,6 +225,7 @@ dg_status setup_host(const dg_params &p, const dg_mesh &m, HostSetup &hs, std::s
   Geometry g;
   dg_status rc = build_geometry(b, m, g, err);
   if (rc) return rc;
+  hs.affine = affine_elements(b, m, g);
   std::vector<double> invJ(g.J.size());
   for (size_t i = 0; i < g.J.size(); ++i) invJ[i] = 1.0 / g.J[i];
   std::vector<double> blk = basis_block(b);
@@ -519,6 +521,7 @@ dg_status dg_create(const dg_params *p, const dg_mesh *m, void *d_workspace, siz
   std::string err;
   rc = setup_host(*p, *m, hs, err);
   if (rc) return fail(rc, err);
+  s->vd.affine = s->vf.affine = hs.affine;
   hipError_t e = setup_device(*p, hs, s->ws, L, s->st);
   if (e == hipSuccess) e = hipStreamSynchronize(s->st);  // the host buffers go out of scope
   if (e != hipSuccess) return device_error(nullptr, e, "dg_create upload");

@@ -44,6 +44,7 @@ struct HostSetup {
   std::vector<double> Ja, invJ, NS, basis, Xs;  // FP64 form
   std::vector<float> fJa, finvJ, fNS, fbasis;   // mixed form
   std::vector<int2> conn;
+  bool affine = false;  // View::affine
   size_t bytes() const {
     return 8 * (Ja.size() + invJ.size() + NS.size() + basis.size() + Xs.size()) +
            4 * (fJa.size() + finvJ.size() + fNS.size() + fbasis.size()) + sizeof(int2) * conn.size();
