@@ -384,7 +384,7 @@ __device__ __forceinline__ void prim2cons(const real *q, real gamma, real *U) {
 // buffer of flux rows (two barriers fewer) measured the same at N = 5 and 3%
 // slower at N = 4.
 // ---------------------------------------------------------------------------
-template <int N, typename real, bool SHOCK, bool LGL, bool NT>
+template <int N, typename real, bool SHOCK, bool LGL, bool NT, int RS>
 __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<real> *views, const int *blk_start,
                                                                       int nreq, View<real> single, int mode) {
   using S = Sz<N>;
@@ -416,7 +416,14 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   const int pa = Pad<n>::at(i, j, k);
   constexpr int upt = (nf + n3 - 1) / n3;  // face nodes per thread
   double Uold[5] = {0, 0, 0, 0, 0};
-  real Un[5], ns[3];
+  // this side's trace: the end node's state on Gauss-Lobatto nodes; on Gauss
+  // nodes recomputed from the state in LDS where the working set streams from
+  // HBM (40 f bytes per node less), read with the neighbour's where the caches
+  // hold it (small meshes, where the sums' latency counted 7 to 10%)
+  constexpr bool stored = !LGL && !NT;
+  constexpr bool ahead = sizeof(real) == sizeof(double);
+  constexpr bool rows_first = !stored || SHOCK;  // the face phase or the indicator reads the state's rows
+  real Uo[5], Un[5], ns[3];
   bool prim = false;
   real Ja[9];
   // the neighbour's trace and the normal at face node fn
@@ -430,7 +437,10 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
     orient_map(c.y & 7, pq % n, pq / n, N, pp, qq);
     const uint32_t in = (uint32_t)c.x * n2 + pp + n * qq;
 #pragma unroll
-    for (int s = 0; s < 5; ++s) Un[s] = (tr + s * Ef)[in];
+    for (int s = 0; s < 5; ++s) {
+      if constexpr (stored) Uo[s] = (tr + s * Ef)[fb + fn];
+      Un[s] = (tr + s * Ef)[in];
+    }
 #pragma unroll
     for (int d = 0; d < 3; ++d) ns[d] = (v.NS + d * Ef)[fb + (v.affine ? f * n2 : fn)];
   };
@@ -439,12 +449,18 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
     for (int c = 0; c < 5; ++c) Uold[c] = ld<NT>(v.U + c * Ev + vi);
     // the first face node's operands beside the state; with more than one per
     // thread (N <= 4) the others' where they are used: held from here they
-    // spilled at N = 4
-    if (a < nf) fetch(a);
+    // spilled at N = 4.  The mixed form, whose waves are more, fetches all of
+    // them and the metrics where it uses them (82 against 68 VGPRs at N = 3, 10%
+    // slower)
+    if (ahead && a < nf) fetch(a);
+    if constexpr (ahead) {
 #pragma unroll
-    for (int c = 0; c < 9; ++c) Ja[c] = ld<NT>(v.Ja + c * Ev + gi);
+      for (int c = 0; c < 9; ++c) Ja[c] = ld<NT>(v.Ja + c * Ev + gi);
+    }
+    if constexpr (rows_first) {
 #pragma unroll
-    for (int c = 0; c < 5; ++c) su[c * Pad<n>::size + pa] = to_real(Uold[c], c, v);
+      for (int c = 0; c < 5; ++c) su[c * Pad<n>::size + pa] = to_real(Uold[c], c, v);
+    }
   }
   if constexpr (SHOCK) {
     real eps = real(0);  // rho p
@@ -478,7 +494,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
       sAl[le] = active ? al : real(0);
     }
   }
-  __syncthreads();
+  if constexpr (rows_first) __syncthreads();
   if constexpr (SHOCK) {
     bool any = false;
 #pragma unroll
@@ -490,18 +506,19 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   }
   if (active) {
     // FillFlux for the six faces of this element
-#pragma unroll
+#pragma unroll (ahead ? upt : 1)
     for (int r = 0; r < upt; ++r) {
       const int fn = a + r * n3;
       if (fn < nf) {
-        if (r > 0) fetch(fn);
+        if (!ahead || r > 0) fetch(fn);
         int f = fn / n2;
         if constexpr (plane_waves) f = __builtin_amdgcn_readfirstlane(f);
         const int pq = fn - f * n2;
-        int base, stride;
-        Pad<n>::face_line(f, pq, base, stride);
-        real Uo[5];
-        face_state<n, LGL>(su, (f & 1) ? sb.lp : sb.lm, base, stride, f & 1, Uo);
+        if constexpr (!stored) {
+          int base, stride;
+          Pad<n>::face_line(f, pq, base, stride);
+          face_state<n, LGL>(su, (f & 1) ? sb.lp : sb.lm, base, stride, f & 1, Uo);
+        }
         const bool primary = prim;
         real Um[5], Us[5], Pm[6], Ps[6];
 #pragma unroll
@@ -518,8 +535,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
         const real ish = real(1) / sh;
         const real nv[3] = {nsv[0] * ish, nsv[1] * ish, nsv[2] * ish};
         real Fs[5];
-        if (v.riemann == 1) riemann_roe(Um, Pm, Us, Ps, nv, gam, Fs, bg);
-        else riemann_llf(Um, Pm, Us, Ps, nv, gam, Fs, bg);
+        riemann<RS>(v.riemann, Um, Pm, Us, Ps, nv, gam, Fs, bg);
 #pragma unroll
         for (int s = 0; s < 5; ++s) sf[s * nf + fn] = primary ? Fs[s] * sh : -(Fs[s] * sh);
       }
@@ -533,7 +549,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   if (active) {
     // the FP64 copy in LDS is exact: read back rather than held through the
     // face phase (those registers spilled at N = 3 to 5)
-    if constexpr (sizeof(real) == sizeof(double)) {
+    if constexpr (rows_first && sizeof(real) == sizeof(double)) {
 #pragma unroll
       for (int c = 0; c < 5; ++c) Uold[c] = su[c * Pad<n>::size + pa];
     }
@@ -541,6 +557,10 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
 #pragma unroll
     for (int c = 0; c < 5; ++c) U[c] = to_real(Uold[c], c, v);
     cons2prim(U, gam, rR, P, bg);
+    if constexpr (!ahead) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) Ja[c] = ld<NT>(v.Ja + c * Ev + gi);
+    }
     iJ = v.invJ[gi];
 #pragma unroll
     for (int c = 0; c < 5; ++c) dUo[c] = (mode == 0 && v.rkA != 0.0) ? ld<NT>(v.dU + c * Ev + vi) : 0.0;
@@ -548,7 +568,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
     flux_adv<1>(U, P, Fy, bg);
     flux_adv<2>(U, P, Fz, bg);
   }
-  __syncthreads();  // the state rows are read above; flux rows cover them
+  if constexpr (rows_first) __syncthreads();  // the state rows are read above; flux rows cover them
   // VolInt: one computational direction at a time
   real V[5] = {0, 0, 0, 0, 0};
 #pragma unroll
@@ -844,7 +864,7 @@ struct VolLds {
 // ---------------------------------------------------------------------------
 // Volume sweep.  From the lifted gradient, which never leaves the chip, it
 // forms (a) at each own face node this side's viscous normal flux
-// H = F_v(prim, g).n, with n in the primary side's orientation, and (b) the
+// H = F_v(prim, g).n shat, with n in the primary side's orientation, and (b) the
 // complete volume integral of F_adv - F_v.  Writes H (4 values per face node:
 // the mass component is zero) and the volume integral (5 per node); with
 // shock capturing also the element's indicator value; with DIAG the
@@ -1326,21 +1346,10 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
             const real ns = sm[L::Ns + dd * nf + fn];
             nsv[dd] = primary ? ns : -ns;
           }
-          const real ish = real(1) / sqrt(nsv[0] * nsv[0] + nsv[1] * nsv[1] + nsv[2] * nsv[2]);
-          const real nv[3] = {nsv[0] * ish, nsv[1] * ish, nsv[2] * ish};
-          const real Pf[6] = {real(0), pf[r][u][0], pf[r][u][1], pf[r][u][2], real(0), real(0)};
           const real muf = pf[r][u][3];
           const real lamf = suth ? muf * v.kappa : lam;
-          real H[5] = {0, 0, 0, 0, 0}, tmp[5];
-          flux_visc<0>(Pf, gt[u], muf, lamf, tmp);
-#pragma unroll
-          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[0];
-          flux_visc<1>(Pf, gt[u], muf, lamf, tmp);
-#pragma unroll
-          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[1];
-          flux_visc<2>(Pf, gt[u], muf, lamf, tmp);
-#pragma unroll
-          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[2];
+          real H[5];
+          flux_visc_face(pf[r][u], gt[u], muf, lamf, nsv, H);
 #pragma unroll
           for (int s = 1; s < 5; ++s) st<NT>(H[s], v.Hv + (s - 1) * Ef + fb + fn);
         }
@@ -1473,11 +1482,8 @@ struct AffLds {
   static constexpr int rows = m1 > m2 ? (m1 > m3 ? m1 : m3) : (m2 > m3 ? m2 : m3);
   static constexpr bool plane_waves = S::n2 == 64 && S::epb == 1;
   static constexpr bool mfma = sizeof(real) == 8 && N == 7;
-  // face nodes per work unit: as in VolLds, but one at N = 7 in the mixed form
-  // (194 against 205 us on 24^3; in FP64 one took 110 against 106 us on 16^3,
-  // at N = 3 122 against 106 on 30^3; two took 302 against 239 us at N = 6 on
-  // 20^3 and 142 against 132 at N = 9 on 12^3, and at N = 5 the same)
-  static constexpr int fpu = (N == 7 && sizeof(real) == 4) ? 1 : VolLds<N, real, false, false>::fpu;
+  static constexpr int minw = N == 1 ? 3 : S::minw;  // N = 1 spills 30 registers at 128
+  static constexpr int fpu = VolLds<N, real, false, false>::fpu;  // face nodes per work unit
   static constexpr int units = nf / fpu, upt = (units + n3 - 1) / n3;
 };
 
@@ -1492,10 +1498,12 @@ struct AffLds {
 // LDS.  16^3 at N = 7: 139 -> 104 us (3.3 TB/s; its LDS accesses and its FP64
 // arithmetic take about 40 us each, which 16 waves per CU overlap in part).
 // The contravariant fluxes formed after the face phase instead of held
-// through it (116 against 124 VGPRs) measured 2% slower.
+// through it (116 against 124 VGPRs) measured 2% slower; one face node per work
+// unit 4% slower at N = 7 and 16% at N = 3, two 27% slower at N = 6 and 7% at
+// N = 9.
 // ---------------------------------------------------------------------------
 template <int N, typename real, bool LGL, bool SUTH, bool NT>
-__global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_volume_affine(const View<real> *views,
+__global__ void __launch_bounds__(Sz<N>::threads, (AffLds<N, real>::minw)) k_volume_affine(const View<real> *views,
                                                                                 const int *blk_start, int nreq,
                                                                                 View<real> single) {
   using S = Sz<N>;
@@ -1635,7 +1643,8 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_volume_affine(c
 #pragma unroll
     for (int f = 0; f < 6; ++f) {
       const int d = f >> 1;
-      if (LGL && lf[d] != ((f & 1) ? n - 1 : 0)) continue;  // l-hat vanishes off the end nodes
+      // (on Gauss-Lobatto nodes l-hat vanishes off the end nodes: skipping
+      // those terms put six branches here and 51 spilled registers at N = 5)
       const real lh = (f & 1) ? sb.lhp[lf[d]] : -sb.lhm[lf[d]];
 #pragma unroll
       for (int s = 0; s < 4; ++s) w[d][s] += lh * sm[L::Avg + s * nf + f * n2 + pqf[d]];
@@ -1717,29 +1726,19 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_volume_affine(c
             }
           }
         }
-        // the unit normal in the primary side's orientation: -+ Ja^d / |Ja^d|
+        // n shat in the primary side's orientation: -+ Ja^d
         const real m0 = d == 0 ? Ja[0] : (d == 1 ? Ja[3] : Ja[6]);
         const real m1 = d == 0 ? Ja[1] : (d == 1 ? Ja[4] : Ja[7]);
         const real m2 = d == 0 ? Ja[2] : (d == 1 ? Ja[5] : Ja[8]);
-        const real im = real(1) / sqrt(m0 * m0 + m1 * m1 + m2 * m2);
 #pragma unroll
         for (int u = 0; u < L::fpu; ++u) {
           const int fn = (2 * d + s0 + u) * n2 + pq;
-          const real sg = ((s0 + u) != 0) == prim[r][u] ? im : -im;
-          const real nv[3] = {m0 * sg, m1 * sg, m2 * sg};
-          const real Pf[6] = {real(0), pf[r][u][0], pf[r][u][1], pf[r][u][2], real(0), real(0)};
+          const real sg = ((s0 + u) != 0) == prim[r][u] ? real(1) : real(-1);
+          const real nsv[3] = {m0 * sg, m1 * sg, m2 * sg};
           const real muf = pf[r][u][3];
           const real lamf = SUTH ? muf * v.kappa : lam;
-          real H[5] = {0, 0, 0, 0, 0}, tmp[5];
-          flux_visc<0>(Pf, gt[u], muf, lamf, tmp);
-#pragma unroll
-          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[0];
-          flux_visc<1>(Pf, gt[u], muf, lamf, tmp);
-#pragma unroll
-          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[1];
-          flux_visc<2>(Pf, gt[u], muf, lamf, tmp);
-#pragma unroll
-          for (int s = 0; s < 5; ++s) H[s] += tmp[s] * nv[2];
+          real H[5];
+          flux_visc_face(pf[r][u], gt[u], muf, lamf, nsv, H);
 #pragma unroll
           for (int s = 1; s < 5; ++s) st<NT>(H[s], v.Hv + (s - 1) * Ef + fb + fn);
         }
@@ -1784,6 +1783,18 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_volume_affine(c
   }
 }
 
+// The surface sweep at N = 6 in FP64: one face node per thread, its operands
+// (the neighbour's trace, n shat, the sum of both sides' viscous fluxes)
+// fetched beside the state and no loop.  That takes 96 VGPRs, so three of the
+// six-wave workgroups share a CU instead of two: 20^3 on Gauss nodes 270 -> 209
+// us (Roe), on Gauss-Lobatto nodes 184 -> 165 us (LLF); the general loop within
+// 96 VGPRs spilled, 344 us.  Roe on Gauss-Lobatto nodes fits two workgroups
+// with 108 VGPRs and spilled at 96 (63 -> 80 us on 14^3): it keeps the loop.  At
+// the other degrees the bound gains no workgroup and the loop is the faster
+// form (by 16% at N = 9, 3% on small meshes).
+template <int N, typename real, int SH, bool LGL, int RS>
+constexpr bool surf_early = N == 6 && sizeof(real) == sizeof(double) && SH != 2 && !(LGL && RS == 1);
+
 // ---------------------------------------------------------------------------
 // Surface sweep of one workgroup of elements: FillFlux from this side's
 // recomputed U trace, the neighbour's stored one and the mean of both sides'
@@ -1795,7 +1806,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_volume_affine(c
 // blend pass after the one-sweep Euler kernel): there is no stored volume
 // integral, the advective one formed here is the whole of it.
 // ---------------------------------------------------------------------------
-template <int N, typename real, int SH, bool LGL, bool SPLIT = false, bool NT = false, bool ONE = false>
+template <int N, typename real, int SH, bool LGL, int RS, bool SPLIT = false, bool NT = false, bool ONE = false>
 __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk, const int mode, const int tid) {
   using S = Sz<N>;
   constexpr int n = S::n, n2 = S::n2, n3 = S::n3, nf = S::nf, epb = S::epb;
@@ -1847,12 +1858,33 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
   // LDS sets.
   constexpr bool exact_lds = sizeof(real) == sizeof(double) && !FV;
   double Uold[5] = {0, 0, 0, 0, 0};
+  constexpr bool early = surf_early<N, real, SH, LGL, RS>;
+  static_assert(!early || nf <= n3, "one face node per thread");
+  real Ue[5], ne[3], He[4] = {0, 0, 0, 0};
+  bool pe = false;
   if (active) {
 #pragma unroll
-    for (int c = 0; c < 5; ++c) {
-      Uold[c] = ld<NT>(v.U + c * Ev + vi);
-      su[c * Pad<n>::size + pa] = to_real(Uold[c], c, v);
+    for (int c = 0; c < 5; ++c) Uold[c] = ld<NT>(v.U + c * Ev + vi);
+    if constexpr (early) {
+      if (a < nf) {
+        const int f = a / n2, pq = a - f * n2;
+        const int2 c = v.conn[e * 6 + f];
+        pe = (c.y >> 3) & 1;
+        int pp, qq;
+        orient_map(c.y & 7, pq % n, pq / n, N, pp, qq);
+        const uint32_t io = fb + a, in = (uint32_t)c.x * n2 + pp + n * qq;
+#pragma unroll
+        for (int s = 0; s < 5; ++s) Ue[s] = (tr + s * Ef)[in];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) ne[d] = (v.NS + d * Ef)[v.affine ? fb + f * n2 : io];
+        if (visc) {
+#pragma unroll
+          for (int s = 0; s < 4; ++s) He[s] = (v.Hv + s * Ef)[io] + (v.Hv + s * Ef)[in];
+        }
+      }
     }
+#pragma unroll
+    for (int c = 0; c < 5; ++c) su[c * Pad<n>::size + pa] = to_real(Uold[c], c, v);
   }
   if (SHOCK && le < epb && a == 0) {
     // blending factor: frozen, or the element's own indicator value, an
@@ -1893,7 +1925,32 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
       }
     }
   }
-  if (active) {
+  if constexpr (early) {
+    if (active && a < nf) {
+      const int f = a / n2;
+      int base, stride;
+      Pad<n>::face_line(f, a - f * n2, base, stride);
+      real Uo[5], Um[5], Us[5], Pm[6], Ps[6], nv[3], Fs[5];
+      face_state<n, LGL>(su, (f & 1) ? sb.lp : sb.lm, base, stride, f & 1, Uo);
+#pragma unroll
+      for (int s = 0; s < 5; ++s) {
+        Um[s] = pe ? Uo[s] : Ue[s];
+        Us[s] = pe ? Ue[s] : Uo[s];
+      }
+      cons2prim(Um, gam, rR, Pm, bg);
+      cons2prim(Us, gam, rR, Ps, bg);
+      const real sh = sqrt(ne[0] * ne[0] + ne[1] * ne[1] + ne[2] * ne[2]);
+      const real ish = pe ? real(1) / sh : real(-1) / sh;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) nv[d] = ne[d] * ish;
+      riemann<RS>(v.riemann, Um, Pm, Us, Ps, nv, gam, Fs, bg);
+#pragma unroll
+      for (int s = 0; s < 5; ++s) {
+        const real F = Fs[s] * sh - (s > 0 ? real(0.5) * He[s > 0 ? s - 1 : 0] : real(0));
+        sS[le][s][a] = pe ? F : -F;
+      }
+    }
+  } else if (active) {
     // FillFlux: Riemann flux of the U traces minus the mean of both sides' H.
     // This side's trace is recomputed from the state (the same bits as the
     // stored one); the neighbour's is read.
@@ -1930,16 +1987,25 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
         nsv[d] = primary ? ns : -ns;
       }
       const real sh = sqrt(nsv[0] * nsv[0] + nsv[1] * nsv[1] + nsv[2] * nsv[2]);
-      const real nv[3] = {nsv[0] / sh, nsv[1] / sh, nsv[2] / sh};
+      const real ish = kScaledVisc<real> ? real(1) / sh : real(0);
+      const real nv[3] = {kScaledVisc<real> ? nsv[0] * ish : nsv[0] / sh, kScaledVisc<real> ? nsv[1] * ish : nsv[1] / sh,
+                          kScaledVisc<real> ? nsv[2] * ish : nsv[2] / sh};
       real Fs[5];
-      if (v.riemann == 1) riemann_roe(Um, Pm, Us, Ps, nv, gam, Fs, bg);
+      if (RS == 2 ? v.riemann == 1 : RS == 1) riemann_roe(Um, Pm, Us, Ps, nv, gam, Fs, bg);
       else riemann_llf(Um, Pm, Us, Ps, nv, gam, Fs, bg);
+      if constexpr (kScaledVisc<real>) {
+#pragma unroll
+        for (int s = 0; s < 5; ++s) Fs[s] *= sh;
+      }
       if (visc) {
 #pragma unroll
         for (int s = 1; s < 5; ++s) Fs[s] -= real(0.5) * ((v.Hv + (s - 1) * Ef)[im] + (v.Hv + (s - 1) * Ef)[is]);
       }
 #pragma unroll
-      for (int s = 0; s < 5; ++s) sS[le][s][fn] = primary ? Fs[s] * sh : -(Fs[s] * sh);
+      for (int s = 0; s < 5; ++s) {
+        if constexpr (kScaledVisc<real>) sS[le][s][fn] = primary ? Fs[s] : -Fs[s];
+        else sS[le][s][fn] = primary ? Fs[s] * sh : -(Fs[s] * sh);
+      }
     }
   }
   __syncthreads();
@@ -2105,12 +2171,12 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
 
 // Surface sweep: SH = 0 without shock capturing; SH = 1 with it, for the
 // workgroups without a blended element (the others are listed for k_blend).
-template <int N, typename real, int SH, bool LGL, bool NT>
-__global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_surface(const View<real> *views, const int *blk_start,
+template <int N, typename real, int SH, bool LGL, bool NT, int RS>
+__global__ void __launch_bounds__(Sz<N>::threads, (surf_early<N, real, SH, LGL, RS> ? 5 : Sz<N>::minw)) k_surface(const View<real> *views, const int *blk_start,
                                                                           int nreq, View<real> single, int mode) {
   int lblk;
   const View<real> v = select_view(views, blk_start, nreq, single, lblk);
-  surface_body<N, real, SH, LGL, false, NT>(v, lblk, mode, threadIdx.x);
+  surface_body<N, real, SH, LGL, RS, false, NT>(v, lblk, mode, threadIdx.x);
 }
 
 // Blend pass: the surface sweep with the FV subcell blend, for the workgroups
@@ -2133,7 +2199,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_blend(const Vie
     for (int idx = blockIdx.x; idx < cnt; idx += gridDim.x) {
       int tid = threadIdx.x;
       asm volatile("" : "+v"(tid));
-      surface_body<N, real, 2, LGL, SPLIT, false, ONE>(v, v.blist[idx], mode, tid);
+      surface_body<N, real, 2, LGL, 2, SPLIT, false, ONE>(v, v.blist[idx], mode, tid);
       __syncthreads();  // LDS is reused by the next listed workgroup
     }
   }
@@ -2148,8 +2214,9 @@ template <int N, typename real, bool SHOCK, bool LGL, bool SPLIT>
 static void volume_sweep(dim3 grid, const View<real> *views, const int *blk_start, int nreq, const View<real> &v0,
                          hipStream_t st) {
   constexpr int threads = VolLds<N, real, SHOCK, SPLIT>::threads;
-  if constexpr (!SHOCK && !SPLIT) {
-    // a mesh of parallelepipeds
+  if constexpr (!SHOCK && !SPLIT && sizeof(real) == sizeof(double)) {
+    // a mesh of parallelepipeds, in FP64 (the mixed form keeps the order of its
+    // roundings, see kScaledVisc; its general sweep reads one node's metrics)
     if (v0.affine && v0.viscous) {
       const int at = Sz<N>::threads;
       if (v0.nt) {
@@ -2172,6 +2239,39 @@ static void volume_sweep(dim3 grid, const View<real> *views, const int *blk_star
       k_volume<N, real, SHOCK, LGL, SPLIT, true><<<grid, threads, 0, st>>>(views, blk_start, nreq, v0);
     else
       k_volume<N, real, SHOCK, LGL, SPLIT, false><<<grid, threads, 0, st>>>(views, blk_start, nreq, v0);
+  }
+}
+
+// the sweeps that form face fluxes, with the Riemann solver of the view (a
+// template flag: together the two took more registers than either, with
+// spills, and the code of both)
+template <int N, typename real, int SH, bool LGL>
+static void surface_sweep(dim3 grid, dim3 block, const View<real> *views, const int *blk_start, int nreq,
+                          const View<real> &v0, int mode, hipStream_t st) {
+  if constexpr (sizeof(real) == sizeof(float)) {  // (the mixed form fits its registers with both)
+    if (v0.nt) k_surface<N, real, SH, LGL, true, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    else k_surface<N, real, SH, LGL, false, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+  } else if (v0.riemann == 1) {
+    if (v0.nt) k_surface<N, real, SH, LGL, true, 1><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    else k_surface<N, real, SH, LGL, false, 1><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+  } else {
+    if (v0.nt) k_surface<N, real, SH, LGL, true, 0><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    else k_surface<N, real, SH, LGL, false, 0><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+  }
+}
+
+template <int N, typename real, bool SHOCK, bool LGL>
+static void euler_sweep(dim3 grid, dim3 block, const View<real> *views, const int *blk_start, int nreq,
+                        const View<real> &v0, int mode, hipStream_t st) {
+  if constexpr (sizeof(real) == sizeof(float)) {
+    if (v0.nt) k_rhs<N, real, SHOCK, LGL, true, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    else k_rhs<N, real, SHOCK, LGL, false, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+  } else if (v0.riemann == 1) {
+    if (v0.nt) k_rhs<N, real, SHOCK, LGL, true, 1><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    else k_rhs<N, real, SHOCK, LGL, false, 1><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+  } else {
+    if (v0.nt) k_rhs<N, real, SHOCK, LGL, true, 0><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    else k_rhs<N, real, SHOCK, LGL, false, 0><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
   }
 }
 
@@ -2218,44 +2318,33 @@ static hipError_t launch_nl(Kernel k, int mode, const View<real> *views, const i
       break;
     case K_RHS:
       // surface sweep (after a volume sweep), or the one-sweep Euler operator
-      if (v0.one && v0.shock) {
-        if constexpr (LGL && N >= 2 && N <= 7) {  // what shock capturing accepts
-          if (v0.nt)
-            k_rhs<N, real, true, true, true><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
-          else
-            k_rhs<N, real, true, true, false><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
-          k_blend<N, real, true, false, true><<<std::min(blocks, kBlendBlocks<N>), block, 0, st>>>(views, nreq, v0, mode);
-        } else {
-          return hipErrorInvalidValue;
-        }
-      } else if (v0.one) {
-        if (v0.nt)
-          k_rhs<N, real, false, LGL, true><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
-        else
-          k_rhs<N, real, false, LGL, false><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
-      } else if (v0.shock) {
+      if (v0.shock) {
         if constexpr (N >= 2 && N <= 7) {  // the degrees shock capturing accepts
-          if (v0.nt)
-            k_surface<N, real, 1, LGL, true><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
-          else
-            k_surface<N, real, 1, LGL, false><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
-          if (v0.split) {
+          const int bb = std::min(blocks, kBlendBlocks<N>);
+          if (v0.one) {
             if constexpr (LGL) {
-              k_blend<N, real, LGL, true><<<std::min(blocks, kBlendBlocks<N>), block, 0, st>>>(views, nreq, v0, mode);
+              euler_sweep<N, real, true, true>(grid, block, views, blk_start, nreq, v0, mode, st);
+              k_blend<N, real, true, false, true><<<bb, block, 0, st>>>(views, nreq, v0, mode);
             } else {
               return hipErrorInvalidValue;
             }
           } else {
-            k_blend<N, real, LGL, false><<<std::min(blocks, kBlendBlocks<N>), block, 0, st>>>(views, nreq, v0, mode);
+            surface_sweep<N, real, 1, LGL>(grid, block, views, blk_start, nreq, v0, mode, st);
+            if (!v0.split) {
+              k_blend<N, real, LGL, false><<<bb, block, 0, st>>>(views, nreq, v0, mode);
+            } else if constexpr (LGL) {
+              k_blend<N, real, LGL, true><<<bb, block, 0, st>>>(views, nreq, v0, mode);
+            } else {
+              return hipErrorInvalidValue;
+            }
           }
         } else {
           return hipErrorInvalidValue;
         }
+      } else if (v0.one) {
+        euler_sweep<N, real, false, LGL>(grid, block, views, blk_start, nreq, v0, mode, st);
       } else {
-        if (v0.nt)
-          k_surface<N, real, 0, LGL, true><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
-        else
-          k_surface<N, real, 0, LGL, false><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+        surface_sweep<N, real, 0, LGL>(grid, block, views, blk_start, nreq, v0, mode, st);
       }
       break;
     default: return hipErrorInvalidValue;

@@ -78,6 +78,48 @@ __device__ __forceinline__ void flux_visc(const real *P, const real *g, real mu,
   F[4] = tau[0] * P[1] + tau[1] * P[2] + tau[2] * P[3] + lambda * g[d * 4 + 3];
 }
 
+// What the sweeps exchange at a face node: this side's viscous flux along the
+// face normal.  FP64: along n shat = m, F[1..3] = tau m, F[4] = u . tau m +
+// lambda grad T . m, formed from the gradients along m and the gradients' m
+// components rather than from the three Cartesian fluxes (half the operations,
+// no square root and division in the volume sweep; the surface sweep adds it
+// to the Riemann flux after that one's scaling by shat).  Mixed form: along the
+// unit normal, summed from the Cartesian fluxes; another order of its FP32
+// roundings moves results by as much as the form's own error (1e-9 to 9e-9 of
+// the state over a few steps), so it keeps this one.
+template <typename real>
+constexpr bool kScaledVisc = sizeof(real) == sizeof(double);
+template <typename real>
+__device__ __forceinline__ void flux_visc_face(const real *u, const real *g, real mu, real lambda, const real *m,
+                                               real *F) {
+  if constexpr (!kScaledVisc<real>) {
+    const real im = real(1) / sqrt(m[0] * m[0] + m[1] * m[1] + m[2] * m[2]);
+    const real nv[3] = {m[0] * im, m[1] * im, m[2] * im};
+    const real P[6] = {real(0), u[0], u[1], u[2], real(0), real(0)};
+    real tmp[5];
+#pragma unroll
+    for (int s = 0; s < 5; ++s) F[s] = real(0);
+    flux_visc<0>(P, g, mu, lambda, tmp);
+#pragma unroll
+    for (int s = 0; s < 5; ++s) F[s] += tmp[s] * nv[0];
+    flux_visc<1>(P, g, mu, lambda, tmp);
+#pragma unroll
+    for (int s = 0; s < 5; ++s) F[s] += tmp[s] * nv[1];
+    flux_visc<2>(P, g, mu, lambda, tmp);
+#pragma unroll
+    for (int s = 0; s < 5; ++s) F[s] += tmp[s] * nv[2];
+    return;
+  }
+  const real div = real(2.0 / 3.0) * (g[0] + g[5] + g[10]);
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const real along = g[a] * m[0] + g[4 + a] * m[1] + g[8 + a] * m[2];
+    const real comp = g[4 * a] * m[0] + g[4 * a + 1] * m[1] + g[4 * a + 2] * m[2];
+    F[1 + a] = mu * (along + comp - div * m[a]);
+  }
+  F[4] = u[0] * F[1] + u[1] * F[2] + u[2] * F[3] + lambda * (g[3] * m[0] + g[7] * m[1] + g[11] * m[2]);
+}
+
 // Sec. 2.1 Eq. sutherland: the viscosity at temperature T, normalised by the
 // reference temperature: mu(T) = mu_ref 1.4042 th^(3/2) / (th + 0.4042), th = T/T_ref
 template <typename real>
@@ -179,9 +221,17 @@ __device__ __forceinline__ void riemann_roe(const real *UL, const real *PL, cons
   for (int d = 0; d < 3; ++d) du[d] = PR[1 + d] - PL[1 + d];
   const real dun = du[0] * nv[0] + du[1] * nv[1] + du[2] * nv[2];
   const real drho = PR[0] - PL[0], dp = PR[4] - PL[4];
-  const real a1 = (dp - rt * ct * dun) / (real(2) * c2);
-  const real a2 = drho - dp / c2;
-  const real a3 = (dp + rt * ct * dun) / (real(2) * c2);
+  real a1, a2, a3;
+  if constexpr (sizeof(real) == sizeof(double)) {
+    const real ic2 = real(1) / c2, h2 = real(0.5) * ic2;
+    a1 = (dp - rt * ct * dun) * h2;
+    a2 = drho - dp * ic2;
+    a3 = (dp + rt * ct * dun) * h2;
+  } else {  // each quotient rounded once in FP32
+    a1 = (dp - rt * ct * dun) / (real(2) * c2);
+    a2 = drho - dp / c2;
+    a3 = (dp + rt * ct * dun) / (real(2) * c2);
+  }
   const real l1 = fabs(un - ct) * a1, l2 = fabs(un) * a2, l3 = fabs(un + ct) * a3;
   const real ls = fabs(un) * rt;
   real dut[3];
@@ -196,6 +246,14 @@ __device__ __forceinline__ void riemann_roe(const real *UL, const real *PL, cons
   Dis[4] = l1 * (Ht - un * ct) + l2 * real(0.5) * q2 + ls * udut + l3 * (Ht + un * ct);
 #pragma unroll
   for (int v = 0; v < 5; ++v) F[v] = real(0.5) * (FL[v] + FR[v]) - real(0.5) * Dis[v];
+}
+
+// RS: 0 local Lax-Friedrichs, 1 Roe, 2 the solver that `which` names
+template <int RS, typename real>
+__device__ __forceinline__ void riemann(int which, const real *UL, const real *PL, const real *UR, const real *PR,
+                                        const real *nv, real gamma, real *F, Bg<real> bg) {
+  if (RS == 1 || (RS == 2 && which == 1)) riemann_roe(UL, PL, UR, PR, nv, gamma, F, bg);
+  else riemann_llf(UL, PL, UR, PR, nv, gamma, F, bg);
 }
 
 }  // namespace dg

@@ -548,13 +548,13 @@ dg_status launch_group(dg_server *sv, Kernel k, int N, const std::vector<Request
 // one RK stage for every active request
 dg_status tick(dg_server *sv) {
   // one group per kernel set: degree, precision, shock capturing, viscosity,
-  // parallelepiped meshes, viscosity law, sweeps per stage, volume form and nodes
+  // Riemann solver, parallelepiped meshes, viscosity law, sweeps per stage, volume form and nodes
   std::map<std::tuple<int, int, int, int, int>, std::vector<Request *>> groups;
   for (int64_t id : sv->active) {
     Request &r = *sv->reqs[id];
     if (r.retiring || r.step >= r.n_steps) continue;
     groups[{r.p.N, r.p.precision, r.p.shock_capturing, r.p.viscous,
-            16 * r.vd.affine + 8 * r.p.viscosity_law + 4 * one_sweep(r.p) + 2 * r.p.volume_flux + r.p.nodes}]
+            32 * r.p.riemann + 16 * r.vd.affine + 8 * r.p.viscosity_law + 4 * one_sweep(r.p) + 2 * r.p.volume_flux + r.p.nodes}]
         .push_back(&r);
   }
   if (groups.empty()) return DG_OK;

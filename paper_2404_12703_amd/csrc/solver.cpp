@@ -225,7 +225,8 @@ dg_status setup_host(const dg_params &p, const dg_mesh &m, HostSetup &hs, std::s
   Geometry g;
   dg_status rc = build_geometry(b, m, g, err);
   if (rc) return rc;
-  hs.affine = affine_elements(b, m, g);
+  // (the mixed form keeps its metrics and the order of its roundings)
+  hs.affine = p.precision == 0 && affine_elements(b, m, g);
   std::vector<double> invJ(g.J.size());
   for (size_t i = 0; i < g.J.size(); ++i) invJ[i] = 1.0 / g.J[i];
   std::vector<double> blk = basis_block(b);
