@@ -1217,29 +1217,69 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
 #pragma unroll
       for (int m = 0; m < npt; ++m) {
 #pragma unroll
-        for (int c = 0; c < 12; ++c) g[m][c] = JG[m][c] * iJe[m];
+        for (int c = 0; c < 12; ++c) {
+          g[m][c] = JG[m][c] * iJe[m];
+          // formed here: sunk into the branch of the dissipation sums, their
+          // arithmetic left every loaded operand live (418 spilled registers at N = 9)
+          if constexpr (DIAG) asm volatile("" : "+v"(g[m][c]));
+        }
       }
     }
   }
   // dissipation sums of Sec. 5.2 at this thread's nodes: w J mu |curl u|^2 and w J mu (div u)^2
-  double dS = 0.0, dD = 0.0, dW = 0.0;
-  if (DIAG && active && visc) {
-    const BasisOffsets o(n);
-    const real *wq = v.basis + o.w;
+  if constexpr (DIAG) {
+    double dS = 0.0, dD = 0.0, dW = 0.0;
+    if (active && visc) {
+      const BasisOffsets o(n);
+      const real *wq = v.basis + o.w;
 #pragma unroll
-    for (int m = 0; m < npt; ++m) {
-      const real *gm = g[m];
-      const double T = (double)sm[L::V + 3 * n3 + a + m * tpe];
-      const double mud = v.visc_law ? sutherland<double>(T, (double)mu, (double)v.rTref) : (double)mu;
-      const double wJ = (double)wq[i] * (double)wq[j] * (double)wq[k0 + m * kstep] / (double)v.invJ[gi + m * gstep];
-      const double wx = (double)gm[1 * 4 + 2] - (double)gm[2 * 4 + 1];
-      const double wy = (double)gm[2 * 4 + 0] - (double)gm[0 * 4 + 2];
-      const double wz = (double)gm[0 * 4 + 1] - (double)gm[1 * 4 + 0];
-      const double dv = (double)gm[0] + (double)gm[5] + (double)gm[10];
-      dS += wJ * mud * (wx * wx + wy * wy + wz * wz);
-      dD += wJ * mud * dv * dv;
-      dW += wJ;
+      for (int m = 0; m < npt; ++m) {
+        const real *gm = g[m];
+        const double T = (double)sm[L::V + 3 * n3 + a + m * tpe];
+        const double mud = v.visc_law ? sutherland<double>(T, (double)mu, (double)v.rTref) : (double)mu;
+        const double wJ = (double)wq[i] * (double)wq[j] * (double)wq[k0 + m * kstep] / (double)v.invJ[gi + m * gstep];
+        const double wx = (double)gm[1 * 4 + 2] - (double)gm[2 * 4 + 1];
+        const double wy = (double)gm[2 * 4 + 0] - (double)gm[0 * 4 + 2];
+        const double wz = (double)gm[0 * 4 + 1] - (double)gm[1 * 4 + 0];
+        const double dv = (double)gm[0] + (double)gm[5] + (double)gm[10];
+        dS += wJ * mud * (wx * wx + wy * wy + wz * wz);
+        dD += wJ * mud * dv * dv;
+        dW += wJ;
+      }
     }
+    // the element's sums in a fixed order (reproducible, no atomics): sixteen
+    // threads each take every sixteenth node, then one adds their sums.  A
+    // dissipation sweep needs nothing past the gradients, so it ends here (the
+    // call on 24^3 at N = 7, 90 us of traces included: 677 us with one thread
+    // adding all nodes and the face fluxes and volume integral written too, 422
+    // us now)
+    __syncthreads();  // the rows read above are covered below
+    constexpr int parts = tpe < 16 ? tpe : 16;
+    // 3 (tpe + 16) doubles per element fit its rows at every degree and precision
+    static_assert(epb * L::rows * sizeof(real) >= epb * 3 * (tpe + 16) * sizeof(double), "sums in LDS");
+    double *sd = (double *)&sA[0][0] + (le < epb ? le : 0) * 3 * (tpe + 16);
+    if (active) {
+      sd[a] = dS;
+      sd[tpe + a] = dD;
+      sd[2 * tpe + a] = dW;
+    }
+    __syncthreads();
+    if (active && a < parts) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c) {
+        double s = 0.0;
+        for (int t = a; t < tpe; t += parts) s += sd[c * tpe + t];
+        sd[3 * tpe + c * 16 + a] = s;
+      }
+    }
+    __syncthreads();
+    if (active && a < 3) {
+      double s = 0.0;
+#pragma unroll
+      for (int t = 0; t < parts; ++t) s += sd[3 * tpe + a * 16 + t];
+      v.diag[3 * e + a] = s;
+    }
+    return;
   }
   if (active) {
     // volume fluxes at each node, projected on the three contravariant directions
@@ -1445,29 +1485,6 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
 #pragma unroll
       for (int c = 0; c < 5; ++c)
         st<NT>(SPLIT ? Vs[m][c] + Vi[m][c] : Vi[m][c], v.Vol + c * Ev + vi + m * tpe);
-  }
-  if constexpr (DIAG) {
-    // the element's dissipation sums in a fixed order (reproducible, no atomics)
-    __syncthreads();
-    // 3 tpe doubles per element fit its rows at every degree and precision
-    double *sd = (double *)&sA[0][0] + (le < epb ? le : 0) * 3 * tpe;
-    if (active) {
-      sd[a] = dS;
-      sd[tpe + a] = dD;
-      sd[2 * tpe + a] = dW;
-    }
-    __syncthreads();
-    if (active && a == 0) {
-      double s0 = 0.0, s1 = 0.0, s2 = 0.0;
-      for (int t = 0; t < tpe; ++t) {
-        s0 += sd[t];
-        s1 += sd[tpe + t];
-        s2 += sd[2 * tpe + t];
-      }
-      v.diag[3 * e] = s0;
-      v.diag[3 * e + 1] = s1;
-      v.diag[3 * e + 2] = s2;
-    }
   }
 }
 
@@ -2311,10 +2328,13 @@ static hipError_t launch_nl(Kernel k, int mode, const View<real> *views, const i
       }
       break;
     case K_DIAG:
-      // the lifting of the volume sweep with the dissipation sums; the
-      // volume integral it also writes is a stage temporary
-      k_volume<N, real, false, LGL, false, false, true>
-          <<<grid, (VolLds<N, real, false, false>::threads), 0, st>>>(views, blk_start, nreq, v0);
+      // the lifting of the volume sweep and the dissipation sums
+      if (v0.nt)
+        k_volume<N, real, false, LGL, false, false, true, true>
+            <<<grid, (VolLds<N, real, false, false>::threads), 0, st>>>(views, blk_start, nreq, v0);
+      else
+        k_volume<N, real, false, LGL, false, false, true, false>
+            <<<grid, (VolLds<N, real, false, false>::threads), 0, st>>>(views, blk_start, nreq, v0);
       break;
     case K_RHS:
       // surface sweep (after a volume sweep), or the one-sweep Euler operator

@@ -119,6 +119,9 @@ __global__ void __launch_bounds__(256) k_finite(const double *U, int64_t count, 
 __global__ void __launch_bounds__(1024) k_sum3(const double *in, int64_t E, double *out) {
   __shared__ double s[3][1024];
   double a0 = 0.0, a1 = 0.0, a2 = 0.0;
+  // eight elements' loads in flight per thread: one after the other, their
+  // latency was most of the kernel's time
+#pragma unroll 8
   for (int64_t e = threadIdx.x; e < E; e += 1024) {
     a0 += in[3 * e];
     a1 += in[3 * e + 1];

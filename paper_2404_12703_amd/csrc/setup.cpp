@@ -239,9 +239,11 @@ std::vector<double> basis_block(const Basis &b) {
 
 namespace {
 
+// fn(0 .. count-1) over host threads, at least `grain` calls on each
 template <class F>
-void parallel_for(int64_t count, F &&fn) {
+void parallel_for(int64_t count, F &&fn, int64_t grain = 1) {
   unsigned nt = std::max(1u, std::min(32u, std::thread::hardware_concurrency()));
+  nt = (unsigned)std::max<int64_t>(1, std::min<int64_t>(nt, count / grain));
   if (count < 64) nt = 1;
   std::vector<std::thread> th;
   int64_t chunk = (count + nt - 1) / nt;
@@ -455,6 +457,7 @@ bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
   const int n = b.n, n2 = n * n, n3 = n2 * n;
   const int64_t E = m.n_elems;
   const int ng = m.n_geo + 1, ng3 = ng * ng * ng;
+  const int64_t grain = 100000 / n3 + 1;  // elements worth a thread of their own
   auto ja = [&](int c, int64_t e) { return g.Ja.data() + ((size_t)c * E + e) * n3; };
   std::vector<double> mean((size_t)9 * E), meanJ(E);
   double xmax = 0.0;
@@ -488,7 +491,7 @@ bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
     const double tol = 2.3e-16 * std::max(1.0, xmax * big / (2.0 * J)) * 2.0 * m.n_geo * m.n_geo * m.n_geo + 1e-15;
     if (off > tol * big || spread(g.J.data() + (size_t)e * n3, J) > 3.0 * tol * J) affine.store(false);
     meanJ[e] = J;
-  });
+  }, grain);
   if (!affine.load()) return false;
   parallel_for(E, [&](int64_t e) {
     for (int c = 0; c < 9; ++c) std::fill(g.Ja.begin() + ((size_t)c * E + e) * n3, g.Ja.begin() + ((size_t)c * E + e + 1) * n3, mean[(size_t)c * E + e]);
@@ -504,7 +507,7 @@ bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
         std::fill(at, at + n2, sg * mean[(size_t)(3 * (pf / 2) + c) * E + pe]);
       }
     }
-  });
+  }, grain);
   return true;
 }
 
