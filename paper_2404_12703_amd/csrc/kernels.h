@@ -24,7 +24,10 @@
 //   k_blend  : (shock capturing) the same for the workgroups holding an
 //              element with a positive blending factor, which k_surface lists
 //              and skips, plus the FV subcell operator.
-// Euler without shock capturing takes one sweep, k_rhs.
+// On meshes of parallelepipeds every kernel reads one node's metrics, and the
+// viscous standard form takes k_volume_affine for its volume sweep (FP64).
+// Euler takes one sweep, k_rhs (with shock capturing then k_blend), unless the
+// blending factors are smoothed over neighbours or the split form is chosen.
 // Traces are ping-ponged between stages because the last sweep reads the
 // neighbours' traces of the old state while writing those of the new one.
 // Layouts are structure-of-arrays with one contiguous (N+1)^3 block per
