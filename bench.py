@@ -350,7 +350,7 @@ def main():
         sbl.profile(False)
         print(json.dumps({"workload": "blast 32^3 N=5 Lobatto, indicator + FV blend, FP64", "steps": args.steps,
                           "value": wb.dof * 5 * args.steps / elb, "unit": "DOF*stage/s",
-                          "k_volume_ms": pb["lift"][0] / pb["lift"][1], "k_surface_ms": pb["rhs"][0] / pb["rhs"][1],
+                          "k_volume_ms": pb["lift"][0] / max(1, pb["lift"][1]), "k_surface_ms": pb["rhs"][0] / pb["rhs"][1],
                           "alpha_pos_fraction": float(np.mean(sbl.alpha() > 0))}), flush=True)
         return
     if args.only_ctgv:
