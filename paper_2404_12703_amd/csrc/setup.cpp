@@ -457,7 +457,7 @@ bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
   const int n = b.n, n2 = n * n, n3 = n2 * n;
   const int64_t E = m.n_elems;
   const int ng = m.n_geo + 1, ng3 = ng * ng * ng;
-  const int64_t grain = 100000 / n3 + 1;  // elements worth a thread of their own
+  const int64_t grain = 8000 / n3 + 1;  // elements worth a thread of their own (about 0.1 ms)
   auto ja = [&](int c, int64_t e) { return g.Ja.data() + ((size_t)c * E + e) * n3; };
   std::vector<double> mean((size_t)9 * E), meanJ(E);
   double xmax = 0.0;
