@@ -382,7 +382,9 @@ __device__ __forceinline__ void prim2cons(const real *q, real gamma, real *U) {
 // and the next U traces.  mode 0: du = A du + dt R, U += B du; mode 1: write
 // R only.  SHOCK: the element's indicator value comes first; a workgroup with
 // a blended element is listed for k_blend and stops.
-// Bound by HBM: 8 (36 + 13 f) bytes per node, f = 6/(N+1) face nodes per node,
+// Bound by HBM: 8 (30 + 13 f) bytes per node, f = 6/(N+1) face nodes per node
+// (28^3 at N = 5: 320 us with one node's metrics, 350 us reading all of them, 4.7
+// TB/s; as two sweeps 210 + 319 us),
 // with every load issued before the phase that precedes its use.  A second
 // buffer of flux rows (two barriers fewer) measured the same at N = 5 and 3%
 // slower at N = 4.
