@@ -129,11 +129,11 @@ struct Geometry {
 int build_geometry(const Basis &b, const dg_mesh &m, Geometry &g, std::string &err);
 
 // Whether every element is a parallelepiped as far as the mesh's coordinates
-// can tell: its metrics and Jacobian vary by no more than rounding the
-// coordinates to double explains.  If so, the metrics of each element are
-// replaced by their mean and the face normals by the primary side's, so that
-// every node of an element holds the same bits and the discrete metric
-// identities stay at round-off.  Otherwise g is unchanged.
+// can tell: its nodes lie where the rounding of the coordinates to double
+// leaves them.  If so, and if that keeps the discrete metric identities at
+// round-off or as close as they are, the metrics of each element are replaced
+// by their mean and the face normals by the primary side's, so that every node
+// of an element holds the same bits.  Otherwise g is unchanged.
 bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g);
 
 // orientation code map (p,q) -> neighbour face coordinates

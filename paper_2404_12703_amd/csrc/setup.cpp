@@ -453,60 +453,135 @@ int build_geometry(const Basis &b, const dg_mesh &m, Geometry &g, std::string &e
   return DG_OK;
 }
 
+// The largest residual of the discrete metric identity
+//   sum_i (D-hat Ja^i)_d + sum_f l-hat (n shat)_d = 0,
+// what a uniform flow's time derivative is made of, in units of its element's
+// largest metric.
+static double identity_residual(const Basis &b, int64_t E, const Geometry &g, int64_t grain) {
+  const int n = b.n, n2 = n * n, n3 = n2 * n;
+  std::vector<double> worst(E);
+  parallel_for(E, [&](int64_t e) {
+    double big = 0.0, res = 0.0;
+    for (int d = 0; d < 3; ++d) {
+      const double *Ja[3], *ns[6];
+      for (int i = 0; i < 3; ++i) Ja[i] = g.Ja.data() + ((size_t)(3 * i + d) * E + e) * n3;
+      for (int f = 0; f < 6; ++f) ns[f] = g.NS.data() + ((size_t)d * E * 6 + e * 6 + f) * n2;
+      for (int a = 0; a < n3; ++a) {
+        const int l[3] = {a % n, (a / n) % n, a / n2}, pq[3] = {a / n, l[0] + n * l[2], a % n2};
+        double s = 0.0;
+        for (int i = 0, st = 1; i < 3; ++i, st *= n) {
+          const double *line = Ja[i] + a - l[i] * st;
+          for (int q = 0; q < n; ++q) s += b.Dhat[l[i] * n + q] * line[q * st];
+          s += b.lhm[l[i]] * ns[2 * i][pq[i]] + b.lhp[l[i]] * ns[2 * i + 1][pq[i]];
+          big = std::max(big, std::fabs(Ja[i][a]));
+        }
+        res = std::max(res, std::fabs(s));
+      }
+    }
+    worst[e] = res / big;
+  }, grain);
+  return *std::max_element(worst.begin(), worst.end());
+}
+
+// Whether every element's geometry nodes lie where the parallelepiped of its
+// corners has them, up to rounding: within 4 eps of the mesh's extent along
+// each axis (boxes and sheared boxes, whose coordinates carry the rounding of
+// their own arithmetic, measured up to 2.3), and the element wide enough that
+// this is below 1e-10 of it.  An axis is held to its own extent: a wave of
+// 1e-4 of the width of thin layers is 1e10 times that.
+static bool parallelepipeds(const dg_mesh &m, int64_t grain) {
+  const int64_t E = m.n_elems;
+  const int n1 = m.n_geo, ng = n1 + 1, ng3 = ng * ng * ng;
+  std::vector<xr> x, w;
+  lobatto_t<xr>(n1, x, w);
+  double tol[3] = {0.0, 0.0, 0.0};
+  for (int64_t e = 0; e < E; ++e)
+    for (int c = 0; c < 3; ++c)
+      for (int t = 0; t < ng3; ++t) tol[c] = std::max(tol[c], std::fabs(m.x_geo[(e * 3 + c) * ng3 + t]));
+  for (double &t : tol) t *= 4.0 * 2.220446049250313e-16;
+  std::atomic<bool> all{true};
+  parallel_for(E, [&](int64_t e) {
+    if (!all.load(std::memory_order_relaxed)) return;
+    for (int c = 0; c < 3; ++c) {
+      const double *X = m.x_geo + (e * 3 + c) * ng3;
+      xr mid = 0, A[3] = {0, 0, 0};  // centre and half edges
+      for (int s = 0; s < 8; ++s) {
+        const xr v = (xr)X[vid(ng, s & 1 ? n1 : 0, s & 2 ? n1 : 0, s & 4 ? n1 : 0)] / 8;
+        mid += v;
+        for (int d = 0; d < 3; ++d) A[d] += (s >> d) & 1 ? v : -v;
+      }
+      const double half = (double)(std::fabs(A[0]) + std::fabs(A[1]) + std::fabs(A[2]));
+      double off = 0.0;
+      for (int k = 0; k < ng; ++k)
+        for (int j = 0; j < ng; ++j)
+          for (int i = 0; i < ng; ++i)
+            off = std::max(off, (double)std::fabs(X[vid(ng, i, j, k)] - (mid + A[0] * x[i] + A[1] * x[j] + A[2] * x[k])));
+      if (!(off <= tol[c] && tol[c] <= 2e-10 * half)) all.store(false);
+    }
+  }, grain);
+  return all.load();
+}
+
 bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
   const int n = b.n, n2 = n * n, n3 = n2 * n;
   const int64_t E = m.n_elems;
-  const int ng = m.n_geo + 1, ng3 = ng * ng * ng;
   const int64_t grain = 8000 / n3 + 1;  // elements worth a thread of their own (about 0.1 ms)
-  auto ja = [&](int c, int64_t e) { return g.Ja.data() + ((size_t)c * E + e) * n3; };
-  std::vector<double> mean((size_t)9 * E), meanJ(E);
-  double xmax = 0.0;
-  for (size_t t = 0; t < (size_t)E * 3 * ng3; ++t) xmax = std::max(xmax, std::fabs(m.x_geo[t]));
-  std::atomic<bool> affine{true};
+  if (!parallelepipeds(m, grain)) return false;
+  std::vector<double> mean((size_t)9 * E), meanJ(E), res(E);
   parallel_for(E, [&](int64_t e) {
-    if (!affine.load(std::memory_order_relaxed)) return;
     auto average = [&](const double *x) {
       xr s = 0;
       for (int a = 0; a < n3; ++a) s += x[a];
       return (double)(s / n3);
     };
-    auto spread = [&](const double *x, double mid) {
-      double s = 0.0;
-      for (int a = 0; a < n3; ++a) s = std::max(s, std::fabs(x[a] - mid));
-      return s;
-    };
-    const double J = average(g.J.data() + (size_t)e * n3);
-    double size[3], M[9], off = 0.0;
-    for (int c = 0; c < 9; ++c) {
-      M[c] = average(ja(c, e));
-      mean[(size_t)c * E + e] = M[c];
-    }
-    for (int i = 0; i < 3; ++i) size[i] = std::sqrt(M[3 * i] * M[3 * i] + M[3 * i + 1] * M[3 * i + 1] + M[3 * i + 2] * M[3 * i + 2]);
-    const double big = std::max(size[0], std::max(size[1], size[2]));
-    for (int c = 0; c < 9; ++c) off = std::max(off, spread(ja(c, e), M[c]));
-    // a coordinate is rounded by eps x / 2, x the mesh's extent; the curl form
-    // differentiates twice (entries up to n_geo^2 / 2 each) and its leading
-    // terms cancel: measured on boxes and sheared boxes up to 0.9 n_geo^3 eps x/h
-    // of the largest metric.  2 J / |Ja^i| is the element's width h along i
-    const double tol = 2.3e-16 * std::max(1.0, xmax * big / (2.0 * J)) * 2.0 * m.n_geo * m.n_geo * m.n_geo + 1e-15;
-    if (off > tol * big || spread(g.J.data() + (size_t)e * n3, J) > 3.0 * tol * J) affine.store(false);
-    meanJ[e] = J;
+    for (int c = 0; c < 9; ++c) mean[(size_t)c * E + e] = average(g.Ja.data() + ((size_t)c * E + e) * n3);
+    meanJ[e] = average(g.J.data() + (size_t)e * n3);
   }, grain);
-  if (!affine.load()) return false;
+  // the primary side's mean metric, outward from element e through its face f
+  auto face = [&](int64_t e, int f, int c) {
+    const int2 cn = g.conn[e * 6 + f];
+    const bool primary = (cn.y >> 3) & 1;
+    const int64_t pe = primary ? e : cn.x / 6;
+    const int pf = primary ? f : cn.x % 6;
+    const double sg = ((pf & 1) ? 1.0 : -1.0) * (primary ? 1.0 : -1.0);
+    return sg * mean[(size_t)(3 * (pf / 2) + c) * E + pe];
+  };
+  // The identity with the means: neighbours' means differ by the rounding of
+  // their coordinates, and a face takes one side's.  Its residual has to be
+  // round-off (4 n^2 eps; D-hat and l-hat hold entries up to n^2 / 2) or no
+  // larger than that of the metrics as they are, which the same rounding
+  // reaches (sheared boxes at n_geo = 7: 1e-13 with the means, 4e-12 without).
+  std::vector<double> row(n, 0.0);
+  for (int l = 0; l < n; ++l)
+    for (int q = 0; q < n; ++q) row[l] += b.Dhat[l * n + q];
   parallel_for(E, [&](int64_t e) {
-    for (int c = 0; c < 9; ++c) std::fill(g.Ja.begin() + ((size_t)c * E + e) * n3, g.Ja.begin() + ((size_t)c * E + e + 1) * n3, mean[(size_t)c * E + e]);
+    double big = 0.0, s = 0.0;
+    for (int c = 0; c < 3; ++c) {
+      double term[3][N_MAX + 1];  // of direction i at index l of its lines
+      for (int i = 0; i < 3; ++i) {
+        const double M = mean[(size_t)(3 * i + c) * E + e], lo = face(e, 2 * i, c), hi = face(e, 2 * i + 1, c);
+        for (int l = 0; l < n; ++l) term[i][l] = row[l] * M + b.lhm[l] * lo + b.lhp[l] * hi;
+        big = std::max(big, std::fabs(M));
+      }
+      for (int k = 0; k < n; ++k)
+        for (int j = 0; j < n; ++j)
+          for (int i = 0; i < n; ++i) s = std::max(s, std::fabs(term[0][i] + term[1][j] + term[2][k]));
+    }
+    res[e] = s / big;
+  }, grain);
+  const double left = *std::max_element(res.begin(), res.end());
+  if (!(left <= 4.0 * n2 * 2.220446049250313e-16) && !(left <= identity_residual(b, E, g, grain))) return false;
+  parallel_for(E, [&](int64_t e) {
+    for (int c = 0; c < 9; ++c) {
+      auto at = g.Ja.begin() + ((size_t)c * E + e) * n3;
+      std::fill(at, at + n3, mean[(size_t)c * E + e]);
+    }
     std::fill(g.J.begin() + (size_t)e * n3, g.J.begin() + (size_t)(e + 1) * n3, meanJ[e]);
-    for (int f = 0; f < 6; ++f) {
-      const int2 cn = g.conn[e * 6 + f];
-      const bool primary = (cn.y >> 3) & 1;
-      const int64_t pe = primary ? e : cn.x / 6;
-      const int pf = primary ? f : cn.x % 6;
-      const double sg = ((pf & 1) ? 1.0 : -1.0) * (primary ? 1.0 : -1.0);
+    for (int f = 0; f < 6; ++f)
       for (int c = 0; c < 3; ++c) {
         auto at = g.NS.begin() + ((size_t)c * E * 6 + e * 6 + f) * n2;
-        std::fill(at, at + n2, sg * mean[(size_t)(3 * (pf / 2) + c) * E + pe]);
+        std::fill(at, at + n2, face(e, f, c));
       }
-    }
   }, grain);
   return true;
 }
