@@ -176,6 +176,13 @@ __device__ __forceinline__ View<real> select_view(const View<real> *views, const
   return rebase(views[r], single.base);
 }
 
+// whether the metrics of an element's first node stand for all (View::affine,
+// which the mixed form never sets: its kernels do not ask)
+template <typename real>
+__device__ __forceinline__ bool one_node(const View<real> &v) {
+  return sizeof(real) == sizeof(double) && v.affine;
+}
+
 template <int N, typename real>
 struct Smem {
   using S = Sz<N>;
@@ -412,7 +419,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   real *const sf = su + rows;
   const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
   const uint32_t vi = (uint32_t)(e * n3 + a), fb = (uint32_t)(e * 6 * n2);
-  const uint32_t gi = v.affine ? (uint32_t)(e * n3) : vi;  // where this node's metrics stand
+  const uint32_t gi = one_node(v) ? (uint32_t)(e * n3) : vi;  // where this node's metrics stand
   const real gam = v.gamma, rR = v.rRgas;
   const Bg<real> bg{v.bg_p, v.bg_H};
   const real *tr = v.cur ? v.Utr1 : v.Utr0;
@@ -447,7 +454,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
       Un[s] = (tr + s * Ef)[in];
     }
 #pragma unroll
-    for (int d = 0; d < 3; ++d) ns[d] = (v.NS + d * Ef)[fb + (v.affine ? f * n2 : fn)];
+    for (int d = 0; d < 3; ++d) ns[d] = (v.NS + d * Ef)[fb + (one_node(v) ? f * n2 : fn)];
   };
   if (active) {
 #pragma unroll
@@ -919,7 +926,7 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
   // (the host keeps every row below 2^31 entries)
   const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
   const uint32_t vi = (uint32_t)(e * n3 + a), fb = (uint32_t)(e * 6 * n2);
-  const uint32_t gi = v.affine ? (uint32_t)(e * n3) : vi, gstep = v.affine ? 0 : tpe;  // where the metrics stand
+  const uint32_t gi = one_node(v) ? (uint32_t)(e * n3) : vi, gstep = one_node(v) ? 0 : tpe;  // where the metrics stand
   const real gam = v.gamma, rR = v.rRgas, mu = v.mu, lam = v.lambda;
   const Bg<real> bg{v.bg_p, v.bg_H};
   const bool visc = v.viscous != 0;  // the same for the whole grid
@@ -975,7 +982,7 @@ __global__ void __launch_bounds__((VolLds<N, real, SHOCK, SPLIT>::threads), (Vol
       tUn[r][u][s] = (tr + s * Ef)[in];
     }
 #pragma unroll
-    for (int dd = 0; dd < 3; ++dd) tNs[r][u][dd] = (v.NS + dd * Ef)[v.affine ? fb + f * n2 : io];
+    for (int dd = 0; dd < 3; ++dd) tNs[r][u][dd] = (v.NS + dd * Ef)[one_node(v) ? fb + f * n2 : io];
   };
   if (npt == 1 && active && visc) {
 #pragma unroll
@@ -1864,7 +1871,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
   const bool active = le < epb && e < v.E;
   const int64_t Ev = v.E * n3, Ef = v.E * 6 * n2;
   const uint32_t vi = (uint32_t)(e * n3 + a), fb = (uint32_t)(e * 6 * n2);
-  const uint32_t gi = v.affine ? (uint32_t)(e * n3) : vi;  // where this node's metrics stand
+  const uint32_t gi = one_node(v) ? (uint32_t)(e * n3) : vi;  // where this node's metrics stand
   const real gam = v.gamma, rR = v.rRgas;
   const Bg<real> bg{v.bg_p, v.bg_H};
   const bool visc = v.viscous != 0;  // the same for the whole grid
@@ -1898,7 +1905,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
 #pragma unroll
         for (int s = 0; s < 5; ++s) Ue[s] = (tr + s * Ef)[in];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) ne[d] = (v.NS + d * Ef)[v.affine ? fb + f * n2 : io];
+        for (int d = 0; d < 3; ++d) ne[d] = (v.NS + d * Ef)[one_node(v) ? fb + f * n2 : io];
         if (visc) {
 #pragma unroll
           for (int s = 0; s < 4; ++s) He[s] = (v.Hv + s * Ef)[io] + (v.Hv + s * Ef)[in];
@@ -2005,7 +2012,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
       real nsv[3];
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        const real ns = (v.NS + d * Ef)[v.affine ? fb + f * n2 : io];
+        const real ns = (v.NS + d * Ef)[one_node(v) ? fb + f * n2 : io];
         nsv[d] = primary ? ns : -ns;
       }
       const real sh = sqrt(nsv[0] * nsv[0] + nsv[1] * nsv[1] + nsv[2] * nsv[2]);
