@@ -383,17 +383,14 @@ __device__ __forceinline__ void prim2cons(const real *q, real gamma, real *U) {
 // Euler, with or without shock capturing: one sweep per stage.  Nothing of
 // the inviscid operator waits for a neighbour's result (the blending factor
 // is local to the element unless it is smoothed), so the state, the metrics
-// and the register cross HBM once: FillFlux (Riemann flux of this side's
-// recomputed U trace and the neighbour's stored one), VolInt of F_adv through
-// LDS one direction at a time, the SurfInt gather, ApplyJac, the stage update
-// and the next U traces.  mode 0: du = A du + dt R, U += B du; mode 1: write
+// and the register cross HBM once: FillFlux (Riemann flux of both sides' U
+// traces), VolInt of F_adv through LDS one direction at a time, the SurfInt
+// gather, ApplyJac, the stage update and the next U traces.  mode 0: du = A du + dt R, U += B du; mode 1: write
 // R only.  SHOCK: the element's indicator value comes first; a workgroup with
 // a blended element is listed for k_blend and stops.
 // Bound by HBM: 8 (30 + 13 f) bytes per node, f = 6/(N+1) face nodes per node
 // (28^3 at N = 5: 320 us with one node's metrics, 350 us reading all of them, 4.7
-// TB/s; as two sweeps 210 + 319 us),
-// with every load issued before the phase that precedes its use.  A second
-// buffer of flux rows (two barriers fewer) measured the same at N = 5 and 3%
+// TB/s; as two sweeps 210 + 319 us).  A second buffer of flux rows (two barriers fewer) measured the same at N = 5 and 3%
 // slower at N = 4.
 // ---------------------------------------------------------------------------
 template <int N, typename real, bool SHOCK, bool LGL, bool NT, int RS>
@@ -428,12 +425,28 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   const int pa = Pad<n>::at(i, j, k);
   constexpr int upt = (nf + n3 - 1) / n3;  // face nodes per thread
   double Uold[5] = {0, 0, 0, 0, 0};
-  // this side's trace: the end node's state on Gauss-Lobatto nodes; on Gauss
-  // nodes recomputed from the state in LDS where the working set streams from
-  // HBM (40 f bytes per node less), read with the neighbour's where the caches
-  // hold it (small meshes, where the sums' latency counted 7 to 10%)
-  constexpr bool stored = !LGL && !NT;
-  constexpr bool ahead = sizeof(real) == sizeof(double);
+  constexpr bool fp64 = sizeof(real) == sizeof(double);
+  // Two orders of the loads.  Late: the state, the metrics and the first face
+  // operands where they are used, the register before the gather; it takes the
+  // fewest registers (N = 8 mixed: 71 VGPRs and two workgroups per CU, early 85
+  // and one, 1.19 times the time; N = 5: early spills 4, 1.10 times).  Early:
+  // all of them beside the state.  It pays with shock capturing, whose
+  // indicator runs meanwhile, and in FP64 at N = 7 (0.80 of the late time at
+  // 1.6 million DOF), N = 3 on Gauss nodes (0.95), N = 1 on Lobatto nodes (0.93),
+  // and at N = 2 to 4 where the working set streams (0.95 on boxes).
+  constexpr bool early = SHOCK || (fp64 && (N == 7 || (N == 3 && !LGL) || (N == 1 && LGL) ||
+                                            (NT && (N == 3 || N == 4 || (N == 2 && LGL)))));
+  constexpr bool ahead = early && fp64;  // the mixed form's metrics and face operands always late
+  // this side's trace: recomputed from the state in LDS (40 f bytes per node
+  // less) where the working set streams from HBM and f is large (N <= 5: 0.90 of
+  // the time with stored ones at N = 1 and 3; N = 6: 1.06), else read with the
+  // neighbour's; of a state in LDS for the indicator anyway, the end node's
+  constexpr bool stored = !(SHOCK || (NT && N <= 5) || (fp64 && N == 1 && LGL));
+  // streaming hints cost 2 to 7% at N <= 2
+  constexpr bool hint = NT && (SHOCK || N > 2 || (fp64 && N == 2 && !LGL));
+  // both sides' operands fetched in the order that the Riemann solver takes
+  // them (by address), not ordered after the loads: 1 to 4% except at N = 1
+  constexpr bool ordered = stored && !(fp64 && N == 1);
   constexpr bool rows_first = !stored || SHOCK;  // the face phase or the indicator reads the state's rows
   real Uo[5], Un[5], ns[3];
   bool prim = false;
@@ -450,24 +463,24 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
     const uint32_t in = (uint32_t)c.x * n2 + pp + n * qq;
 #pragma unroll
     for (int s = 0; s < 5; ++s) {
-      if constexpr (stored) Uo[s] = (tr + s * Ef)[fb + fn];
-      Un[s] = (tr + s * Ef)[in];
+      if constexpr (stored) Uo[s] = (tr + s * Ef)[ordered && !prim ? in : fb + fn];
+      Un[s] = (tr + s * Ef)[ordered && !prim ? fb + fn : in];
     }
 #pragma unroll
     for (int d = 0; d < 3; ++d) ns[d] = (v.NS + d * Ef)[fb + (one_node(v) ? f * n2 : fn)];
   };
   if (active) {
+    if constexpr (early || rows_first) {
 #pragma unroll
-    for (int c = 0; c < 5; ++c) Uold[c] = ld<NT>(v.U + c * Ev + vi);
+      for (int c = 0; c < 5; ++c) Uold[c] = ld<hint>(v.U + c * Ev + vi);
+    }
     // the first face node's operands beside the state; with more than one per
     // thread (N <= 4) the others' where they are used: held from here they
-    // spilled at N = 4.  The mixed form, whose waves are more, fetches all of
-    // them and the metrics where it uses them (82 against 68 VGPRs at N = 3, 10%
-    // slower)
+    // spilled at N = 4
     if (ahead && a < nf) fetch(a);
     if constexpr (ahead) {
 #pragma unroll
-      for (int c = 0; c < 9; ++c) Ja[c] = ld<NT>(v.Ja + c * Ev + gi);
+      for (int c = 0; c < 9; ++c) Ja[c] = ld<hint>(v.Ja + c * Ev + gi);
     }
     if constexpr (rows_first) {
 #pragma unroll
@@ -535,8 +548,8 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
         real Um[5], Us[5], Pm[6], Ps[6];
 #pragma unroll
         for (int s = 0; s < 5; ++s) {
-          Um[s] = primary ? Uo[s] : Un[s];
-          Us[s] = primary ? Un[s] : Uo[s];
+          Um[s] = ordered || primary ? Uo[s] : Un[s];
+          Us[s] = ordered || primary ? Un[s] : Uo[s];
         }
         cons2prim(Um, gam, rR, Pm, bg);
         cons2prim(Us, gam, rR, Ps, bg);
@@ -553,15 +566,23 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
       }
     }
   }
-  // 1/J and the RK register, loaded before the volume integral: their latency
-  // overlaps it, and the register's loads precede its stores
+  // 1/J and the RK register: early before the volume integral, late before the
+  // gather; their latency overlaps it, and the register's loads precede its stores
   real iJ = real(0);
   double dUo[5] = {0, 0, 0, 0, 0};
+  auto load_register = [&]() {
+    iJ = v.invJ[gi];
+#pragma unroll
+    for (int c = 0; c < 5; ++c) dUo[c] = (mode == 0 && v.rkA != 0.0) ? ld<hint>(v.dU + c * Ev + vi) : 0.0;
+  };
   real Fx[5], Fy[5], Fz[5];
   if (active) {
     // the FP64 copy in LDS is exact: read back rather than held through the
     // face phase (those registers spilled at N = 3 to 5)
-    if constexpr (rows_first && sizeof(real) == sizeof(double)) {
+    if constexpr (!early && !rows_first) {
+#pragma unroll
+      for (int c = 0; c < 5; ++c) Uold[c] = ld<hint>(v.U + c * Ev + vi);
+    } else if constexpr (rows_first && fp64) {
 #pragma unroll
       for (int c = 0; c < 5; ++c) Uold[c] = su[c * Pad<n>::size + pa];
     }
@@ -571,11 +592,9 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
     cons2prim(U, gam, rR, P, bg);
     if constexpr (!ahead) {
 #pragma unroll
-      for (int c = 0; c < 9; ++c) Ja[c] = ld<NT>(v.Ja + c * Ev + gi);
+      for (int c = 0; c < 9; ++c) Ja[c] = ld<hint>(v.Ja + c * Ev + gi);
     }
-    iJ = v.invJ[gi];
-#pragma unroll
-    for (int c = 0; c < 5; ++c) dUo[c] = (mode == 0 && v.rkA != 0.0) ? ld<NT>(v.dU + c * Ev + vi) : 0.0;
+    if constexpr (early) load_register();
     flux_adv<0>(U, P, Fx, bg);
     flux_adv<1>(U, P, Fy, bg);
     flux_adv<2>(U, P, Fz, bg);
@@ -604,6 +623,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   }
   double Unew[5] = {0, 0, 0, 0, 0};
   if (active) {
+    if constexpr (!early) load_register();
     // SurfInt gather (one writer per entry) and ApplyJac
     const int pqf[3] = {j + n * k, i + n * k, i + n * j};
     const int lf[3] = {i, j, k};
@@ -636,9 +656,9 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
         // the first stage (A = 0) does not read the register: whatever it
         // holds (a restored state, an aborted step) cannot leak into the step
         const double du = (v.rkA != 0.0 ? v.rkA * dUo[c] : 0.0) + v.dt * R[c];
-        st<NT>(du, v.dU + c * Ev + vi);
+        st<hint>(du, v.dU + c * Ev + vi);
         Unew[c] = Uold[c] + v.rkB * du;
-        st<NT>(Unew[c], v.U + c * Ev + vi);
+        st<hint>(Unew[c], v.U + c * Ev + vi);
       }
     }
   }
@@ -661,7 +681,7 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
         real t[5];
         face_state<n, LGL>(su, (f & 1) ? sb.lp : sb.lm, base, stride, f & 1, t);
 #pragma unroll
-        for (int c = 0; c < 5; ++c) st<NT>(t[c], trn + c * Ef + fb + fn);
+        for (int c = 0; c < 5; ++c) st<hint>(t[c], trn + c * Ef + fb + fn);
       }
     }
   }
@@ -2292,14 +2312,18 @@ static void surface_sweep(dim3 grid, dim3 block, const View<real> *views, const 
 template <int N, typename real, bool SHOCK, bool LGL>
 static void euler_sweep(dim3 grid, dim3 block, const View<real> *views, const int *blk_start, int nreq,
                         const View<real> &v0, int mode, hipStream_t st) {
+  // on Lobatto nodes at N <= 2 the recomputed traces (an end node's state) pay from
+  // one workgroup per CU on, small meshes lose by the state's way through LDS
+  // (N = 2 mixed: 1.05 times the time at 78 workgroups, 0.96 at a thousand)
+  const bool nt = v0.nt || (!SHOCK && LGL && N <= 2 && grid.x >= 256);
   if constexpr (sizeof(real) == sizeof(float)) {
-    if (v0.nt) k_rhs<N, real, SHOCK, LGL, true, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    if (nt) k_rhs<N, real, SHOCK, LGL, true, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
     else k_rhs<N, real, SHOCK, LGL, false, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
   } else if (v0.riemann == 1) {
-    if (v0.nt) k_rhs<N, real, SHOCK, LGL, true, 1><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    if (nt) k_rhs<N, real, SHOCK, LGL, true, 1><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
     else k_rhs<N, real, SHOCK, LGL, false, 1><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
   } else {
-    if (v0.nt) k_rhs<N, real, SHOCK, LGL, true, 0><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
+    if (nt) k_rhs<N, real, SHOCK, LGL, true, 0><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
     else k_rhs<N, real, SHOCK, LGL, false, 0><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
   }
 }
