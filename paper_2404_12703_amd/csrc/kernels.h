@@ -1832,17 +1832,19 @@ __global__ void __launch_bounds__(Sz<N>::threads, (AffLds<N, real>::minw)) k_vol
   }
 }
 
-// The surface sweep at N = 6 in FP64: one face node per thread, its operands
-// (the neighbour's trace, n shat, the sum of both sides' viscous fluxes)
-// fetched beside the state and no loop.  That takes 96 VGPRs, so three of the
+// The surface sweep at N = 6 in FP64 where the working set streams from HBM: one
+// face node per thread, its operands (the neighbour's trace, n shat, the sum of
+// both sides' viscous fluxes) fetched beside the state and no loop.  That takes 96 VGPRs, so three of the
 // six-wave workgroups share a CU instead of two: 20^3 on Gauss nodes 270 -> 209
 // us (Roe), on Gauss-Lobatto nodes 184 -> 165 us (LLF); the general loop within
 // 96 VGPRs spilled, 344 us.  Roe on Gauss-Lobatto nodes fits two workgroups
 // with 108 VGPRs and spilled at 96 (63 -> 80 us on 14^3): it keeps the loop.  At
 // the other degrees the bound gains no workgroup and the loop is the faster
-// form (by 16% at N = 9, 3% on small meshes).
-template <int N, typename real, int SH, bool LGL, int RS>
-constexpr bool surf_early = N == 6 && sizeof(real) == sizeof(double) && SH != 2 && !(LGL && RS == 1);
+// form (by 16% at N = 9).  Meshes that the caches hold fill the workgroups less
+// and take the loop too: with Roe's solver on Gauss nodes the fetch cost 8% of a
+// step at 6^3 (4 x 4 x 4) and 6% at 9^3.
+template <int N, typename real, int SH, bool LGL, int RS, bool NT>
+constexpr bool surf_early = NT && N == 6 && sizeof(real) == sizeof(double) && SH != 2 && !(LGL && RS == 1);
 
 // ---------------------------------------------------------------------------
 // Surface sweep of one workgroup of elements: FillFlux from this side's
@@ -1907,7 +1909,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
   // LDS sets.
   constexpr bool exact_lds = sizeof(real) == sizeof(double) && !FV;
   double Uold[5] = {0, 0, 0, 0, 0};
-  constexpr bool early = surf_early<N, real, SH, LGL, RS>;
+  constexpr bool early = surf_early<N, real, SH, LGL, RS, NT>;
   static_assert(!early || nf <= n3, "one face node per thread");
   real Ue[5], ne[3], He[4] = {0, 0, 0, 0};
   bool pe = false;
@@ -2221,7 +2223,7 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
 // Surface sweep: SH = 0 without shock capturing; SH = 1 with it, for the
 // workgroups without a blended element (the others are listed for k_blend).
 template <int N, typename real, int SH, bool LGL, bool NT, int RS>
-__global__ void __launch_bounds__(Sz<N>::threads, (surf_early<N, real, SH, LGL, RS> ? 5 : Sz<N>::minw)) k_surface(const View<real> *views, const int *blk_start,
+__global__ void __launch_bounds__(Sz<N>::threads, (surf_early<N, real, SH, LGL, RS, NT> ? 5 : Sz<N>::minw)) k_surface(const View<real> *views, const int *blk_start,
                                                                           int nreq, View<real> single, int mode) {
   int lblk;
   const View<real> v = select_view(views, blk_start, nreq, single, lblk);
