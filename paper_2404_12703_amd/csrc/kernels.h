@@ -1997,6 +1997,9 @@ __device__ __forceinline__ void surface_body(const View<real> &v, const int lblk
       riemann<RS>(v.riemann, Um, Pm, Us, Ps, nv, gam, Fs, bg);
 #pragma unroll
       for (int s = 0; s < 5; ++s) {
+        // rounded twice as in the loop below: a request's bits do not depend on
+        // whether its batch streams
+#pragma clang fp contract(off)
         const real F = Fs[s] * sh - (s > 0 ? real(0.5) * He[s > 0 ? s - 1 : 0] : real(0));
         sS[le][s][a] = pe ? F : -F;
       }
