@@ -169,7 +169,7 @@ __device__ __forceinline__ View<real> select_view(const View<real> *views, const
     lblk = single.remap ? xcd_block(blockIdx.x, gridDim.x) : blockIdx.x;
     return single;
   }
-  const int b = blockIdx.x;
+  const int b = blockIdx.x + blk_start[0];  // a launch may take a range of its group's requests
   int r = 0;
   while (r + 1 < nreq && b >= blk_start[r + 1]) ++r;
   lblk = b - blk_start[r];
@@ -2298,11 +2298,11 @@ static void volume_sweep(dim3 grid, const View<real> *views, const int *blk_star
 
 // the sweeps that form face fluxes, with the Riemann solver of the view (a
 // template flag: together the two took more registers than either, with
-// spills, and the code of both)
+// spills, and the code of both; the mixed form fits its registers with both)
 template <int N, typename real, int SH, bool LGL>
 static void surface_sweep(dim3 grid, dim3 block, const View<real> *views, const int *blk_start, int nreq,
                           const View<real> &v0, int mode, hipStream_t st) {
-  if constexpr (sizeof(real) == sizeof(float)) {  // (the mixed form fits its registers with both)
+  if constexpr (sizeof(real) == sizeof(float)) {
     if (v0.nt) k_surface<N, real, SH, LGL, true, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
     else k_surface<N, real, SH, LGL, false, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
   } else if (v0.riemann == 1) {
