@@ -64,3 +64,12 @@ def test_identity_of_recognised_meshes(driver, tmp_path, N, ngeo, K, shear):  # 
     affine, spread, closure = _run(driver, tmp_path, m, N, 0)
     assert affine == 1 and spread == 0.0
     assert closure <= 1e-12
+
+
+@pytest.mark.parametrize("N,ngeo", [(1, 1), (4, 4), (7, 1), (9, 9)])
+def test_oblique_lattice(driver, tmp_path, N, ngeo):  # noqa: F811
+    """all nine metrics nonzero; the box stays its period"""
+    m = W.box_mesh((3, 2, 3), 0.0, 2 * np.pi, ngeo, rotate=True)
+    m.x_geo = np.einsum("dc,ecg->edg", np.array([[-1.0, -1, 0], [-1, 0, 1], [0, 2, 1]]), m.x_geo)
+    affine, spread, closure = _run(driver, tmp_path, m, N, 0)
+    assert affine == 1 and spread == 0.0 and closure <= 1e-12
