@@ -2272,10 +2272,14 @@ static void volume_sweep(dim3 grid, const View<real> *views, const int *blk_star
     // a mesh of parallelepipeds, in FP64 (the mixed form keeps the order of its
     // roundings, see kScaledVisc; its general sweep reads one node's metrics)
     if (v0.affine && v0.viscous) {
+      // streaming hints where the working set streams: 2 to 5% of a pass at N = 3 to
+      // 9 (26^3 at N = 5: 4.87 -> 4.71 ms, the surface sweep's share as much as its
+      // own); at N <= 2 they made the sweep 15 to 19% slower
+      constexpr bool hints = N >= 3;
       const int at = Sz<N>::threads;
-      if (v0.nt) {
-        if (v0.visc_law) k_volume_affine<N, real, LGL, true, true><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
-        else k_volume_affine<N, real, LGL, false, true><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
+      if (hints && v0.nt) {
+        if (v0.visc_law) k_volume_affine<N, real, LGL, true, hints><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
+        else k_volume_affine<N, real, LGL, false, hints><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
       } else {
         if (v0.visc_law) k_volume_affine<N, real, LGL, true, false><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
         else k_volume_affine<N, real, LGL, false, false><<<grid, at, 0, st>>>(views, blk_start, nreq, v0);
