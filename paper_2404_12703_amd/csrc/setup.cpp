@@ -483,14 +483,10 @@ static double identity_residual(const Basis &b, int64_t E, const Geometry &g, in
   return *std::max_element(worst.begin(), worst.end());
 }
 
-// Whether every element's geometry nodes lie where the parallelepiped of its
-// corners has them, up to rounding: within 4 eps of the mesh's extent along
-// each axis (boxes and sheared boxes, whose coordinates carry the rounding of
-// their own arithmetic, measured up to 2.3), and the element wide enough that
-// this is below 1e-10 of it.  An axis is held to its own extent: a wave of
-// 1e-4 of the width of thin layers is 1e10 times that.
-static bool parallelepipeds(const dg_mesh &m, int64_t grain) {
+bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
+  const int n = b.n, n2 = n * n, n3 = n2 * n;
   const int64_t E = m.n_elems;
+  const int64_t grain = 8000 / n3 + 1;  // elements worth a thread of their own (about 0.1 ms)
   const int n1 = m.n_geo, ng = n1 + 1, ng3 = ng * ng * ng;
   std::vector<xr> x, w;
   lobatto_t<xr>(n1, x, w);
@@ -499,9 +495,13 @@ static bool parallelepipeds(const dg_mesh &m, int64_t grain) {
     for (int c = 0; c < 3; ++c)
       for (int t = 0; t < ng3; ++t) tol[c] = std::max(tol[c], std::fabs(m.x_geo[(e * 3 + c) * ng3 + t]));
   for (double &t : tol) t *= 4.0 * 2.220446049250313e-16;
-  std::atomic<bool> all{true};
-  parallel_for(E, [&](int64_t e) {
-    if (!all.load(std::memory_order_relaxed)) return;
+  // Whether the element's geometry nodes lie where the parallelepiped of its
+  // corners has them, up to rounding: within 4 eps of the mesh's extent along
+  // each axis (boxes and sheared boxes, whose coordinates carry the rounding of
+  // their own arithmetic, measured up to 2.3), and the element wide enough that
+  // this is below 1e-10 of it.  An axis is held to its own extent: a wave of
+  // 1e-4 of the width of thin layers is 1e10 times that.
+  auto parallelepiped = [&](int64_t e) {
     for (int c = 0; c < 3; ++c) {
       const double *X = m.x_geo + (e * 3 + c) * ng3;
       xr mid = 0, A[3] = {0, 0, 0};  // centre and half edges
@@ -516,27 +516,27 @@ static bool parallelepipeds(const dg_mesh &m, int64_t grain) {
         for (int j = 0; j < ng; ++j)
           for (int i = 0; i < ng; ++i)
             off = std::max(off, (double)std::fabs(X[vid(ng, i, j, k)] - (mid + A[0] * x[i] + A[1] * x[j] + A[2] * x[k])));
-      if (!(off <= tol[c] && tol[c] <= 2e-10 * half)) all.store(false);
+      if (!(off <= tol[c] && tol[c] <= 2e-10 * half)) return false;
     }
-  }, grain);
-  return all.load();
-}
-
-bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
-  const int n = b.n, n2 = n * n, n3 = n2 * n;
-  const int64_t E = m.n_elems;
-  const int64_t grain = 8000 / n3 + 1;  // elements worth a thread of their own (about 0.1 ms)
-  if (!parallelepipeds(m, grain)) return false;
+    return true;
+  };
   std::vector<double> mean((size_t)9 * E), meanJ(E), res(E);
+  std::atomic<bool> all{true};
   parallel_for(E, [&](int64_t e) {
-    auto average = [&](const double *x) {
+    if (!all.load(std::memory_order_relaxed)) return;
+    if (!parallelepiped(e)) {
+      all.store(false);
+      return;
+    }
+    auto average = [&](const double *v) {
       xr s = 0;
-      for (int a = 0; a < n3; ++a) s += x[a];
+      for (int a = 0; a < n3; ++a) s += v[a];
       return (double)(s / n3);
     };
     for (int c = 0; c < 9; ++c) mean[(size_t)c * E + e] = average(g.Ja.data() + ((size_t)c * E + e) * n3);
     meanJ[e] = average(g.J.data() + (size_t)e * n3);
   }, grain);
+  if (!all.load()) return false;
   // the primary side's mean metric, outward from element e through its face f
   auto face = [&](int64_t e, int f, int c) {
     const int2 cn = g.conn[e * 6 + f];
@@ -568,7 +568,7 @@ bool affine_elements(const Basis &b, const dg_mesh &m, Geometry &g) {
           for (int i = 0; i < n; ++i) s = std::max(s, std::fabs(term[0][i] + term[1][j] + term[2][k]));
     }
     res[e] = s / big;
-  }, grain);
+  }, 4 * grain);
   const double left = *std::max_element(res.begin(), res.end());
   if (!(left <= 4.0 * n2 * 2.220446049250313e-16) && !(left <= identity_residual(b, E, g, grain))) return false;
   parallel_for(E, [&](int64_t e) {
