@@ -388,10 +388,13 @@ __device__ __forceinline__ void prim2cons(const real *q, real gamma, real *U) {
 // gather, ApplyJac, the stage update and the next U traces.  mode 0: du = A du + dt R, U += B du; mode 1: write
 // R only.  SHOCK: the element's indicator value comes first; a workgroup with
 // a blended element is listed for k_blend and stops.
-// Bound by HBM: 8 (30 + 13 f) bytes per node, f = 6/(N+1) face nodes per node
-// (28^3 at N = 5: 320 us with one node's metrics, 350 us reading all of them, 4.7
-// TB/s; as two sweeps 210 + 319 us).  A second buffer of flux rows (two barriers fewer) measured the same at N = 5 and 3%
-// slower at N = 4.
+// Reading all metrics it is bound by HBM: 8 (30 + 13 f) bytes per node, f =
+// 6/(N+1) face nodes per node, 4.7 TB/s (28^3 at N = 5: 350 us; as two sweeps 210
+// + 319 us).  With one node's metrics, 320 us, no single unit bounds it: 263 bytes
+// per node measured (3.9 TB/s), FP64 at 0.18 of its peak, the LDS index unit
+// active in 0.62 of the CU-busy cycles, and four waves per SIMD that wait half
+// of theirs at the barriers between the phases.  A second buffer of flux rows
+// (two barriers fewer) measured the same at N = 5 and 3% slower at N = 4.
 // ---------------------------------------------------------------------------
 template <int N, typename real, bool SHOCK, bool LGL, bool NT, int RS>
 __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<real> *views, const int *blk_start,
@@ -1544,8 +1547,9 @@ struct AffLds {
 // direction (12 sums per source node instead of 36 products and 36 sums) and
 // applies the metrics once per node, and the nine metric rows and the face
 // normals take neither HBM traffic (98 of 262 bytes per node at N = 7) nor
-// LDS.  16^3 at N = 7: 139 -> 104 us (3.3 TB/s; its LDS accesses and its FP64
-// arithmetic take about 40 us each, which 16 waves per CU overlap in part).
+// LDS.  16^3 at N = 7: 139 -> 104 us.  Bound by LDS: its index unit is active in
+// 0.66 of the CU-busy cycles, 0.17 of them bank conflicts, with FP64 at 0.26 of its
+// peak and 148 bytes per node measured (3.0 TB/s).
 // The contravariant fluxes formed after the face phase instead of held
 // through it (116 against 124 VGPRs) measured 2% slower; one face node per work
 // unit 4% slower at N = 7 and 16% at N = 3, two 27% slower at N = 6 and 7% at

@@ -413,10 +413,9 @@ hipError_t solver_advance(dg_solver *s, int nsteps, double dt) {
   return s->mixed ? advance_impl<float>(s, nsteps, dt) : advance_impl<double>(s, nsteps, dt);
 }
 
-// One volume sweep of the current state with the dissipation sums on (stage
-// temporaries only: the volume integral and the viscous face fluxes), the
-// per-element sums into diag[E][3], their fixed-order total into sums[3],
-// and the two rates of Sec. 5.2 on the host.
+// One volume sweep of the current state up to its gradients, with the
+// dissipation sums: the per-element sums into diag[E][3], their fixed-order
+// total into sums[3], and the two rates of Sec. 5.2 on the host.
 hipError_t dissipation_sweep(dg_solver *s, double *diag, double *sums, double out[2]) {
   hipError_t e = hipSuccess;
   auto sweep = [&](auto &v) {

@@ -1,7 +1,8 @@
 """GPU parity of the kernels' parallelepiped path with the oracle: box and
-sheared meshes, relabelled, at every degree, both node families, Sutherland's
-law, the mixed form, workgroups that the last elements do not fill, and the
-other operators (Euler, split form, blend), which read one node's metrics."""
+stretched box meshes, relabelled, at every degree, both node families,
+Sutherland's law, workgroups that the last elements do not fill, and the other
+operators (Euler, split form, blend), which read one node's metrics.  (The mixed
+form has no such path: its case holds it to its bound on the same meshes.)"""
 import numpy as np
 import pytest
 
