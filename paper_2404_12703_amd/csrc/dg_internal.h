@@ -26,11 +26,6 @@ template <typename real>
 struct View {
   using value_type = real;
   int64_t E;        // elements
-  // (affine stands here to come with the first scalar load of a launch: the
-  // addresses of the metrics wait for it)
-  int affine;       // every element is a parallelepiped (affine_elements): its metrics, 1/J and each
-                    // face's n*shat are the same at every node, and the kernels read the first node's
-  int one;          // one sweep per stage (one_sweep): no volume sweep, no stored volume integral
   double *U;        // [5][E][n3]
   double *dU;       // [5][E][n3]   low-storage RK register
   double *R;        // [5][E][n3]   output of the time derivative (rhs mode), else null
@@ -64,6 +59,9 @@ struct View {
   int cur;          // trace buffer read this stage (0: Utr0, 1: Utr1)
   int bpar;         // entry of bcnt this surface sweep counts in; it clears the other
   int viscous, riemann, source, shock;
+  int affine;       // every element is a parallelepiped (affine_elements): its metrics, 1/J and each
+                    // face's n*shat are the same at every node, and the kernels read the first node's
+  int one;          // one sweep per stage (one_sweep): no volume sweep, no stored volume integral
   int split;        // split-form volume integral with Pirozzoli's two-point flux (Gauss-Lobatto)
   int visc_law;     // 0 constant viscosity, 1 Sutherland's law
   int alpha_smooth; // 1: raise alpha to half the largest face neighbour's indicator value
