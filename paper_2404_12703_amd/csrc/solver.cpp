@@ -128,10 +128,10 @@ Layout make_layout(const dg_params &p, int64_t E, int part) {
   L.NS = take(geo, 3 * E * 6 * n2 * rs);
   L.Utr0 = take(st, 5 * E * 6 * n2 * rs);
   L.Utr1 = take(st, 5 * E * 6 * n2 * rs);
-  // two sweeps exchange each side's viscous face flux (4 values per face node,
-  // viscous only) and the volume integral (5 per node)
+  // the two sweeps exchange each side's viscous face flux (4 values per face
+  // node, viscous only) and the volume integral (5 per node)
   L.Hv = take(st && p.viscous, 4 * E * 6 * n2 * rs);
-  L.Vol = take(st && !one_sweep(p), 5 * E * n3 * rs);
+  L.Vol = take(st && (p.viscous || p.shock_capturing || p.volume_flux), 5 * E * n3 * rs);
   // per-element dissipation sums of dg_dissipation (viscous only)
   L.diag = take(st && p.viscous, 3 * E * sizeof(double));
   L.conn = take(geo, 6 * E * sizeof(int2));
