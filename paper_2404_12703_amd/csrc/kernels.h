@@ -445,8 +445,9 @@ __global__ void __launch_bounds__(Sz<N>::threads, Sz<N>::minw) k_rhs(const View<
   // the time with stored ones at N = 1 and 3; N = 6: 1.06), else read with the
   // neighbour's; of a state in LDS for the indicator anyway, the end node's
   constexpr bool stored = !(SHOCK || (NT && N <= 5) || (fp64 && N == 1 && LGL));
-  // streaming hints cost 2 to 7% at N <= 2
-  constexpr bool hint = NT && (SHOCK || N > 2 || (fp64 && N == 2 && !LGL));
+  // streaming hints cost 2 to 15% at N <= 2, and 3 to 11% in FP64 at N = 8 and 9
+  // from 4 to 8 million nodes on; else they are worth 1 to 11%
+  constexpr bool hint = NT && (SHOCK || (N > 2 && !(fp64 && N >= 8)));
   // both sides' operands fetched in the order that the Riemann solver takes
   // them (by address), not ordered after the loads: 1 to 4% except at N = 1
   constexpr bool ordered = stored && !(fp64 && N == 1);
@@ -2328,7 +2329,10 @@ static void euler_sweep(dim3 grid, dim3 block, const View<real> *views, const in
   // on Lobatto nodes at N <= 2 the recomputed traces (an end node's state) pay from
   // one workgroup per CU on, small meshes lose by the state's way through LDS
   // (N = 2 mixed: 1.05 times the time at 78 workgroups, 0.96 at a thousand)
-  const bool nt = v0.nt || (!SHOCK && LGL && N <= 2 && grid.x >= 256);
+  // and at N = 4 both forms of streaming pay up to a few million nodes only (FP64
+  // 0.97 of the time at 1.6 million, 1.03 at 8 million; mixed 0.95 at 3.6, 1.02 at 8)
+  const bool large4 = !SHOCK && N == 4 && (int64_t)grid.x * Sz<N>::epb * Sz<N>::n3 >= 5000000;
+  const bool nt = (v0.nt && !large4) || (!SHOCK && LGL && N <= 2 && grid.x >= 256);
   if constexpr (sizeof(real) == sizeof(float)) {
     if (nt) k_rhs<N, real, SHOCK, LGL, true, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
     else k_rhs<N, real, SHOCK, LGL, false, 2><<<grid, block, 0, st>>>(views, blk_start, nreq, v0, mode);
